@@ -26,6 +26,7 @@ DEVICE = ["-x", "hip", f"--offload-arch={ARCH}", "-Xclang", "-target-feature",
 SOURCES = [
     ("st_plan.cpp", []),
     ("st_kernels.hip", DEVICE),
+    ("st_dense.hip", DEVICE),
     ("st_exec.hip", DEVICE),
 ]
 

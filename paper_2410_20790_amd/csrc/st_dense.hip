@@ -1,0 +1,450 @@
+// Dense convolutions of the reference pass (gfx950): implicit GEMM on MFMA
+// whose operands go from global memory straight into LDS.
+//
+// The reference frame evaluates every output pixel, so a tile's rows are
+// consecutive pixels and its gathered rows follow from the geometry.  What
+// bounds these layers is streaming (the f32 state and the emitted rows of a
+// 1x1 layer) or the chain load -> LDS -> MFMA of a long reduction with few
+// tiles; both want many bytes in flight per CU and little per-tile work:
+//
+//  - The staged operands bypass the registers (16-byte global-to-LDS loads).
+//    S stages are kept in S separate LDS arrays, so a stage's reads are known
+//    not to alias the loads in flight and no wait but the counted one is
+//    needed: one counted wait and one barrier per stage, with S - 1 stages
+//    of loads outstanding.
+//  - A staged row is 128 bytes in eight 16-byte slots; slot s of row r holds
+//    the row's vector s ^ (r & 7) (weights: an equivalent permutation), set
+//    by the address each lane loads from, so the MFMA operand reads are
+//    conflict-free without padding.
+//  - The weights are the MFMA's first operand: a lane's accumulators are then
+//    consecutive channels of one pixel, and with the weight rows of two
+//    16-channel blocks interleaved four by four, eight of them -- the lane
+//    stores 32 bytes of state and 16 bytes of rows directly.  The accumulators
+//    never go through LDS and the epilogue has no barrier.
+//  - One block per tile (no persistent loop): a tile's loads never wait for
+//    another tile's stores.  Blocks are dealt round-robin over the XCDs, so
+//    each XCD takes a contiguous range of tiles, the channel tiles of one
+//    pixel tile next to each other (they read the same pixels).
+//
+// Against the persistent register-staged 64x64 kernel that these layers took
+// before (ResNet-50 at 1024x2048, bf16, us per layer): 1x1 64->256 with
+// residual on 131072 pixels 93 -> 74 (285 MB, 3.9 TB/s), 1x1 512->128 on
+// 32768 23 -> 16, 3x3 256 on 8192 40 (with its split epilogue) -> 21; the
+// whole reference pass 2.05 -> 1.45 ms.
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "st_device.h"
+#include "st_kernels.h"
+
+namespace st {
+
+namespace {
+
+constexpr int kRowBytes = 128;  // a staged row: 64 half or 32 f32 columns
+constexpr int kDenseXcd = 8;
+
+// Which input rows an offset reads: a 1x1 kernel has one row per pixel; with
+// a channel count that is a multiple of the stage's columns a stage lies
+// within one offset; otherwise every lane walks its own (offset, channel).
+enum { kSrcPoint = 0, kSrcAligned = 1, kSrcAny = 2 };
+
+__device__ __forceinline__ void load_to_lds(const void* g, char* lds) {
+  __builtin_amdgcn_global_load_lds(
+      (__attribute__((address_space(1))) const uint32_t*)(uintptr_t)g,
+      (__attribute__((address_space(3))) uint32_t*)lds, 16, 0, 0);
+}
+
+// Wait until at most N of this wave's vector-memory operations are
+// outstanding (and its LDS reads are done), then meet the block's waves.
+template <int N>
+__device__ __forceinline__ void stage_ready() {
+  static_assert(N < 64, "vmcnt");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// One thread's share of the staged loads: PQ pixel vectors and WQ weight
+// vectors per stage.
+template <typename T, int KIND, int NW, int PQ, int WQ>
+struct DenseLoader {
+  static constexpr int VEC = 16 / (int)sizeof(T);
+  static constexpr int KC = kRowBytes / (int)sizeof(T);
+  const T* prow[PQ];  // the pixel vectors' input rows at offset k, or NULL
+  const T* wrow[WQ];  // the weight vectors' rows, or NULL
+  int iy[PQ], ix[PQ], nb[PQ];  // window origins, image * Hi
+  int k, ci, wc;      // offset and channel; column of the weight row
+  int next;           // (kSrcAligned) columns left of offset k
+  int wave;
+
+  __device__ __forceinline__ void rows_at(const ConvArgs& a) {
+    const int ky = k / a.g.kw, kx = k - ky * a.g.kw;
+#pragma unroll
+    for (int q = 0; q < PQ; ++q) {
+      const int y = iy[q] + ky, x = ix[q] + kx;
+      const bool in = k < a.K && y >= 0 && y < a.g.Hi && x >= 0 && x < a.g.Wi;
+      prow[q] = in ? (const T*)a.din +
+                         (int64_t)((nb[q] + y) * a.g.Wi + x) * a.cin_p
+                   : nullptr;
+    }
+  }
+
+  // st: the first stage
+  __device__ __forceinline__ void init(const ConvArgs& a, int64_t m0, int n0,
+                                       int st, int lane, int wave_) {
+    wave = wave_;
+    const int lr = lane >> 3, slot = lane & 7;
+    const unsigned hwo = (unsigned)a.g.Ho * (unsigned)a.g.Wo;
+#pragma unroll
+    for (int q = 0; q < PQ; ++q) {
+      const int64_t o = m0 + (q * NW + wave) * 8 + lr;
+      const unsigned op = o < a.capO ? (unsigned)o : 0u;
+      const unsigned n = op / hwo, rem = op - n * hwo;
+      const unsigned oy = rem / (unsigned)a.g.Wo;
+      const unsigned ox = rem - oy * (unsigned)a.g.Wo;
+      nb[q] = (int)n * a.g.Hi;
+      iy[q] = (int)oy * a.g.sh - a.g.ph;
+      ix[q] = o < a.capO ? (int)ox * a.g.sw - a.g.pw : -(1 << 28);
+    }
+    k = KIND == kSrcPoint ? 0 : st * KC / a.cin_p;
+    next = (k + 1) * a.cin_p - st * KC;
+    ci = st * KC - k * a.cin_p + (slot ^ lr) * VEC;
+    if (KIND == kSrcAny) {
+      while (ci >= a.cin_p) {
+        ci -= a.cin_p;
+        ++k;
+      }
+    }
+    rows_at(a);
+    wc = st * KC + (slot ^ ((lr & 3) | ((wave & 1) << 2))) * VEC;
+#pragma unroll
+    for (int q = 0; q < WQ; ++q) {
+      const int n = n0 + (q * NW + wave) * 8 + lr;
+      wrow[q] = n < a.cout_p ? (const T*)a.w + (int64_t)n * a.ktot_p : nullptr;
+    }
+  }
+
+  // Issues the next stage's loads into the stage buffer `buf` (pixel rows,
+  // then weight rows); past the reduction's end they read zeros.
+  template <int BM>
+  __device__ __forceinline__ void issue(const ConvArgs& a, char* buf) {
+    const T* zero = (const T*)a.zero;
+#pragma unroll
+    for (int q = 0; q < PQ; ++q) {
+      const bool ok = prow[q] && (KIND != kSrcPoint || ci < a.cin_p);
+      load_to_lds(ok ? prow[q] + ci : zero,
+                  buf + (q * NW + wave) * 8 * kRowBytes);
+    }
+#pragma unroll
+    for (int q = 0; q < WQ; ++q) {
+      const bool ok = wrow[q] && wc < (int)a.ktot_p;
+      load_to_lds(ok ? wrow[q] + wc : zero,
+                  buf + (BM + (q * NW + wave) * 8) * kRowBytes);
+    }
+    wc += KC;
+    ci += KC;
+    if (KIND == kSrcAligned) {
+      next -= KC;
+      if (next == 0) {
+        next = a.cin_p;
+        ci -= a.cin_p;
+        ++k;
+        rows_at(a);
+      }
+    } else if (KIND == kSrcAny) {
+      if (ci >= a.cin_p) {
+        do {
+          ci -= a.cin_p;
+          ++k;
+        } while (ci >= a.cin_p);
+        rows_at(a);
+      }
+    }
+  }
+};
+
+// One stage's products from the stage buffer: WM pixels (in blocks of 16,
+// from row pr) by WN channels (weight rows from wr).
+template <typename T, int IM, int JN>
+__device__ __forceinline__ void stage_products(const char* buf, int pr,
+                                               int wr, int l16, int lg,
+                                               v4f (&acc)[IM][JN]) {
+#pragma unroll
+  for (int kk = 0; kk < 2; ++kk) {
+    const int slot = ((kk * 4 + lg) ^ (l16 & 7)) * 16;
+    uint4 pv[IM], wv[JN];
+#pragma unroll
+    for (int i = 0; i < IM; ++i)
+      pv[i] = *(const uint4*)(buf + (pr + i * 16 + l16) * kRowBytes + slot);
+#pragma unroll
+    for (int j = 0; j < JN; ++j)
+      wv[j] = *(const uint4*)(buf + (wr + (j >> 1) * 32 + (l16 >> 2) * 8 +
+                                     (j & 1) * 4 + (l16 & 3)) *
+                                        kRowBytes +
+                              slot);
+#pragma unroll
+    for (int i = 0; i < IM; ++i) {
+#pragma unroll
+      for (int j = 0; j < JN; ++j) {
+        if constexpr (sizeof(T) == 4) {
+          const float4 w = __builtin_bit_cast(float4, wv[j]);
+          const float4 p = __builtin_bit_cast(float4, pv[i]);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, p.x,
+                                                           acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, p.y,
+                                                           acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, p.z,
+                                                           acc[i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, p.w,
+                                                           acc[i][j], 0, 0, 0);
+        } else if constexpr (__is_same(T, _Float16)) {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+              __builtin_bit_cast(v8h, wv[j]), __builtin_bit_cast(v8h, pv[i]),
+              acc[i][j], 0, 0, 0);
+        } else {
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(v8bf, wv[j]), __builtin_bit_cast(v8bf, pv[i]),
+              acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+  }
+}
+
+// One turn of the stage ring: stage `rd` has arrived once at most AHEAD
+// later loads of this wave are outstanding; the loads of the stage S - 1
+// ahead go to `wr`, which every wave finished reading before the barrier.
+template <typename T, int BM, int AHEAD, int IM, int JN, class Loader>
+__device__ __forceinline__ void stage_turn(const ConvArgs& a, Loader& ld,
+                                           const char* __restrict__ rd,
+                                           char* __restrict__ wr, int pr,
+                                           int wrow, int l16, int lg,
+                                           v4f (&acc)[IM][JN]) {
+  stage_ready<AHEAD>();
+  ld.template issue<BM>(a, wr);
+  stage_products<T, IM, JN>(rd, pr, wrow, l16, lg, acc);
+}
+
+// Tile of BM pixels by BN channels in waves of WM by WN, S stages in LDS.
+// SPLIT: block row y reduces its part of the stages and writes f32 partial
+// rows part[y][pixel][channel], which the split epilogue sums and finishes.
+template <typename T, int KIND, int BM, int BN, int WM, int WN, int S,
+          bool SPLIT>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_dense_conv(ConvArgs a, int tiles_n,
+                                                    int tiles, int chunk) {
+  constexpr int WAVES_N = BN / WN, NW = BM / WM * WAVES_N;
+  constexpr int PQ = BM / 8 / NW, WQ = BN / 8 / NW, L = PQ + WQ;
+  constexpr int IM = WM / 16, JN = WN / 16;
+  constexpr int KC = kRowBytes / (int)sizeof(T);
+  static_assert(PQ * 8 * NW == BM && WQ * 8 * NW == BN && NW % 2 == 0 && JN % 2 == 0, "waves");
+  static_assert(S >= 2 && S <= 4, "stages");
+  constexpr int STAGE = (BM + BN) * kRowBytes;
+  __shared__ __align__(128) char s0[STAGE];
+  __shared__ __align__(128) char s1[STAGE];
+  __shared__ __align__(128) char s2[S > 2 ? STAGE : 128];
+  __shared__ __align__(128) char s3[S > 3 ? STAGE : 128];
+
+  // this XCD's contiguous range of tiles, channel tiles fastest
+  const int t = (int)(blockIdx.x % kDenseXcd) * chunk +
+                (int)(blockIdx.x / kDenseXcd);
+  if ((int)(blockIdx.x / kDenseXcd) >= chunk || t >= tiles) return;
+  const int tm = t / tiles_n;
+  const int64_t m0 = (int64_t)tm * BM;
+  const int n0 = (t - tm * tiles_n) * BN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int l16 = lane & 15, lg = lane >> 4;
+  const int nst = (a.K * a.cin_p + KC - 1) / KC;
+  const int st0 = SPLIT ? (int)blockIdx.y * nst / (int)gridDim.y : 0;
+  const int st1 = SPLIT ? ((int)blockIdx.y + 1) * nst / (int)gridDim.y : nst;
+
+  DenseLoader<T, KIND, NW, PQ, WQ> ld;
+  ld.init(a, m0, n0, st0, lane, wave);
+
+  // the lane's pixels and channels: pixel block i -> pixel pm + 16 i,
+  // channel pair p -> channels cn + 32 p + [0, 8)
+  const int64_t pm = m0 + wm * WM + l16;
+  const int cn = n0 + wn * WN + lg * 8;
+  const int cout_p = a.cout_p;
+
+  v4f acc[IM][JN];
+#pragma unroll
+  for (int i = 0; i < IM; ++i)
+#pragma unroll
+    for (int j = 0; j < JN; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+
+  // the residual rows are requested first: they arrive with the first stage
+  const T* dskip = !SPLIT && a.mskip ? (const T*)a.dskip : nullptr;
+  constexpr int SKV = (int)sizeof(T) / 2;  // 16-byte vectors per 8 channels
+  uint4 sk[JN / 2][IM][SKV];
+#pragma unroll
+  for (int p = 0; p < JN / 2; ++p)
+#pragma unroll
+    for (int i = 0; i < IM; ++i) {
+      const int64_t o = pm + 16 * i;
+      const int c = cn + 32 * p;
+#pragma unroll
+      for (int v = 0; v < SKV; ++v) {
+        sk[p][i][v] = make_uint4(0u, 0u, 0u, 0u);
+        if (dskip && o < a.capO && c < cout_p)
+          sk[p][i][v] = ((const uint4*)(dskip + o * cout_p + c))[v];
+      }
+    }
+
+  ld.template issue<BM>(a, s0);
+  if constexpr (S > 2) ld.template issue<BM>(a, s1);
+  if constexpr (S > 3) ld.template issue<BM>(a, s2);
+  constexpr int AH = (S - 2) * L;
+  const int pr = wm * WM, wr = BM + wn * WN;
+  for (int st = st0; st < st1; st += S) {
+    char* const last = S == 2 ? s1 : S == 3 ? s2 : s3;
+    stage_turn<T, BM, AH>(a, ld, s0, last, pr, wr, l16, lg, acc);
+    if (st + 1 >= st1) break;
+    stage_turn<T, BM, AH>(a, ld, s1, s0, pr, wr, l16, lg, acc);
+    if constexpr (S > 2) {
+      if (st + 2 >= st1) break;
+      stage_turn<T, BM, AH>(a, ld, s2, s1, pr, wr, l16, lg, acc);
+    }
+    if constexpr (S > 3) {
+      if (st + 3 >= st1) break;
+      stage_turn<T, BM, AH>(a, ld, s3, s2, pr, wr, l16, lg, acc);
+    }
+  }
+
+  if constexpr (SPLIT) {
+    float* part = a.part + (int64_t)blockIdx.y * a.capO * cout_p;
+#pragma unroll
+    for (int p = 0; p < JN / 2; ++p)
+#pragma unroll
+      for (int i = 0; i < IM; ++i) {
+        const int64_t o = pm + 16 * i;
+        const int c = cn + 32 * p;
+        if (o >= a.capO || c >= cout_p) continue;
+        *(v4f*)(part + o * cout_p + c) = acc[i][2 * p];
+        *(v4f*)(part + o * cout_p + c + 4) = acc[i][2 * p + 1];
+      }
+    return;
+  }
+  // epilogue: bias, residual row, activation; state and row stores
+  T* dout = (T*)a.dout;
+  with_act(a.act, [&](auto act_tag) {
+    constexpr int ACT = decltype(act_tag)::value;
+#pragma unroll
+    for (int p = 0; p < JN / 2; ++p) {
+      const int c = cn + 32 * p;
+      if (c >= cout_p) continue;
+      float bias[8];
+      load8f(a.bias + c, bias);
+#pragma unroll
+      for (int i = 0; i < IM; ++i) {
+        const int64_t o = pm + 16 * i;
+        if (o >= a.capO) continue;
+        float v[8], f[8];
+        Vec8<T>::load((const T*)sk[p][i], f);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          v[e] = acc[i][2 * p + (e >> 2)][e & 3] + bias[e] + f[e];
+        if (a.mode != kModeLinear) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = state_round(a.p16, v[e]);
+          if (a.p16) {
+            state_store8(a.P, true, o * cout_p + c, v);
+          } else {
+            // the next reader of the state is another frame: streamed past
+            // the caches, which keep the rows the next layer reads
+            v4f* d = (v4f*)(a.P + o * cout_p + c);
+            __builtin_nontemporal_store(v4f{v[0], v[1], v[2], v[3]}, d);
+            __builtin_nontemporal_store(v4f{v[4], v[5], v[6], v[7]}, d + 1);
+          }
+          if (a.mode == kModeStateOnly) continue;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = act_c<ACT>(v[e]);
+        }
+        (void)Vec8<T>::store(dout + o * cout_p + c, v);
+      }
+    }
+  });
+}
+
+template <typename T, int BM, int BN, int WM, int WN, int S,
+          bool SPLIT = false>
+void dense_launch(hipStream_t s, const ConvArgs& a, int splits = 1) {
+  constexpr int KC = kRowBytes / (int)sizeof(T);
+  constexpr int NT = (BM / WM) * (BN / WN) * 64;
+  const int tiles_n = (a.cout_p + BN - 1) / BN;
+  const int tiles = (int)((a.capO + BM - 1) / BM) * tiles_n;
+  const int chunk = (tiles + kDenseXcd - 1) / kDenseXcd;
+  const dim3 grid(chunk * kDenseXcd, splits);
+  if (a.K == 1)
+    k_dense_conv<T, kSrcPoint, BM, BN, WM, WN, S, SPLIT>
+        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk);
+  else if (a.cin_p % KC == 0)
+    k_dense_conv<T, kSrcAligned, BM, BN, WM, WN, S, SPLIT>
+        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk);
+  else
+    k_dense_conv<T, kSrcAny, BM, BN, WM, WN, S, SPLIT>
+        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk);
+}
+
+// Tile shape by the tiles a launch has for the chip's 256 CUs (measured on
+// the layers of a ResNet-50 at 1024x2048, bf16, us):
+//  - 128x128, 3 stages, where that still makes 224 tiles: half the operand
+//    traffic of 64x64 (512->256 on 32768 pixels: 27 against 32; 1024->512 on
+//    8192: 18 against 24), one block of eight waves per CU;
+//  - 128x64 where that makes 224 tiles: two blocks per CU with 3 stages (3x3
+//    256 on 8192 pixels: 21 against 28 for 128x128), three with 2 stages when
+//    the tiles go round the chip several times (3x3 64 on 131072: 27 against
+//    30 with 3 stages);
+//  - 64x64 with 4 stages else (3x3 512 on 2048 pixels: 28 against 35), and
+//    128x32 for at most 32 channels, where half of a 64-channel tile would
+//    be padding.
+// With fewer than 128 tiles of 64x64 a long reduction is split, enough for
+// about 256 blocks, at least 8 stages each.
+template <typename T>
+int dense_conv(hipStream_t s, const ConvArgs& a) {
+  constexpr int KC = kRowBytes / (int)sizeof(T);
+  const int64_t m128 = (a.capO + 127) / 128, m64 = (a.capO + 63) / 64;
+  const int64_t n64 = (a.cout_p + 63) / 64, n128 = (a.cout_p + 127) / 128;
+  const int nst = (a.K * a.cin_p + KC - 1) / KC;
+  if (a.cout_p <= 32 && m128 >= 224) {
+    dense_launch<T, 128, 32, 32, 32, 3>(s, a);
+    return 1;
+  }
+  if (a.cout_p > 64 && m128 * n128 >= 224) {
+    dense_launch<T, 128, 128, 64, 32, 3>(s, a);
+    return 1;
+  }
+  if (m128 * n64 >= 1024) {
+    dense_launch<T, 128, 64, 32, 32, 2>(s, a);
+    return 1;
+  }
+  if (m128 * n64 >= 224) {
+    dense_launch<T, 128, 64, 32, 32, 3>(s, a);
+    return 1;
+  }
+  int splits = 1;
+  if (a.split_max > 1 && m64 * n64 < 128) {
+    splits = (int)((256 + m64 * n64 - 1) / (m64 * n64));
+    splits = splits < a.split_max ? splits : a.split_max;
+    splits = splits < nst / 8 ? splits : nst / 8;
+  }
+  if (splits > 1) {
+    dense_launch<T, 64, 64, 32, 32, 4, true>(s, a, splits);
+    return splits;
+  }
+  dense_launch<T, 64, 64, 32, 32, 4>(s, a);
+  return 1;
+}
+
+}  // namespace
+
+int launch_dense_conv(hipStream_t s, int dtype, const ConvArgs& a) {
+  if (dtype == 0) return dense_conv<float>(s, a);
+  if (dtype == 1) return dense_conv<_Float16>(s, a);
+  return dense_conv<bf16_t>(s, a);
+}
+
+}  // namespace st

@@ -204,7 +204,16 @@ struct ConvArgs {
   // maximum is kept (rowmax NULL)
   int dense;
   Geo g;
+  int dense_splits;  // splits of the dense pass's partial rows (0: not split)
 };
+// Dense pass: the convolution of every pixel (st_dense.hip).  Returns the
+// number of reduction splits it wrote partial rows for (1: finished).  It
+// takes rows whose 16-byte vectors lie within one pixel (not half-precision
+// rows of 4 channels).
+inline bool dense_conv_rows(int dtype, const ConvArgs& a) {
+  return a.cin_p % (dtype == 0 ? 4 : 8) == 0;
+}
+int launch_dense_conv(hipStream_t s, int dtype, const ConvArgs& a);
 // Returns false (and launches nothing) when a.zero is missing or misaligned.
 bool launch_conv_gemm(const Prof& pf, hipStream_t s, int dtype,
                       const ConvArgs& a);

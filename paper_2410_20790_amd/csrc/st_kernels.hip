@@ -22,65 +22,10 @@
 
 #include <cstdint>
 
+#include "st_device.h"
 #include "st_kernels.h"
 
 namespace st {
-
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-
-struct bf16_t {
-  uint16_t v;
-};
-
-// ------------------------------------------------------------ conversions
-__device__ __forceinline__ float to_f(float x) { return x; }
-__device__ __forceinline__ float to_f(_Float16 x) { return (float)x; }
-__device__ __forceinline__ float to_f(bf16_t x) {
-  return __uint_as_float((uint32_t)x.v << 16);
-}
-template <typename T> __device__ __forceinline__ T from_f(float x);
-template <> __device__ __forceinline__ float from_f<float>(float x) {
-  return x;
-}
-template <> __device__ __forceinline__ _Float16 from_f<_Float16>(float x) {
-  return (_Float16)x;  // hardware conversion, round to nearest even
-}
-template <> __device__ __forceinline__ bf16_t from_f<bf16_t>(float x) {
-  // hardware conversion (gfx950), round to nearest even
-  return bf16_t{__builtin_bit_cast(uint16_t, (__bf16)x)};
-}
-template <typename T> __device__ __forceinline__ T zero_v() {
-  return from_f<T>(0.f);
-}
-
-// Activation f: 0 identity, 1 ReLU, 2 SiLU (x / (1 + e^-x)).
-template <int ACT>
-__device__ __forceinline__ float act_c(float x) {
-  if constexpr (ACT == 1)
-    return __builtin_amdgcn_fmed3f(x, 0.f, __builtin_inff());  // max(x, 0)
-  else if constexpr (ACT == 2)
-    return x / (1.f + expf(-x));
-  else
-    return x;
-}
-__device__ __forceinline__ float act_f(float x, int a) {
-  if (a == 1) return act_c<1>(x);
-  if (a == 2) return act_c<2>(x);
-  return x;
-}
-// Calls f(std::integral_constant<int, ACT>{}) for the activation act, so
-// that f's body is built once per activation.
-template <class F>
-__device__ __forceinline__ void with_act(int act, F&& f) {
-  if (act == 1)
-    f(std::integral_constant<int, 1>{});
-  else if (act == 2)
-    f(std::integral_constant<int, 2>{});
-  else
-    f(std::integral_constant<int, 0>{});
-}
 
 // ------------------------------------------------------------ reductions
 __device__ __forceinline__ unsigned wave_sum(unsigned v) {
@@ -793,113 +738,6 @@ __device__ __forceinline__ void lds_store16<bf16_t>(bf16_t* dst, uint4 v) {
 }
 
 constexpr int kGemmBM = 64, kGemmBN = 64, kXcd = 8, kCUs = 256;
-
-// 8 consecutive storage elements <-> 8 floats (16- or 32-byte aligned).
-template <typename T> struct Vec8;
-template <> struct Vec8<float> {
-  __device__ __forceinline__ static void load(const float* p, float* f) {
-    const float4 a = *(const float4*)p, b = *(const float4*)(p + 4);
-    f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w;
-    f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-  }
-  // stores the rounded values, returns their largest magnitude
-  __device__ __forceinline__ static float store(float* p, const float* f) {
-    *(float4*)p = make_float4(f[0], f[1], f[2], f[3]);
-    *(float4*)(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
-    float m = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(f[e]));
-    return m;
-  }
-};
-template <typename T> struct Vec8Half {
-  __device__ __forceinline__ static void load(const T* p, float* f) {
-    const uint4 v = *(const uint4*)p;
-    const T* h = (const T*)&v;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) f[e] = to_f(h[e]);
-  }
-  // stores the rounded values, returns their largest magnitude: rounding
-  // to nearest is monotone and odd, so that is the rounded largest
-  // magnitude of the unrounded values (one conversion instead of eight)
-  __device__ __forceinline__ static float store(T* p, const float* f) {
-    uint4 v;
-    T* h = (T*)&v;
-    float m = 0.f;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      h[e] = from_f<T>(f[e]);
-      m = fmaxf(m, fabsf(f[e]));
-    }
-    *(uint4*)p = v;
-    return to_f(from_f<T>(m));
-  }
-};
-template <> struct Vec8<_Float16> : Vec8Half<_Float16> {};
-template <> struct Vec8<bf16_t> : Vec8Half<bf16_t> {};
-
-
-__device__ __forceinline__ void load8f(const float* p, float* f) {
-  Vec8<float>::load(p, f);
-}
-__device__ __forceinline__ void store8f(float* p, const float* f) {
-  *(float4*)p = make_float4(f[0], f[1], f[2], f[3]);
-  *(float4*)(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
-}
-
-// Pre-activation state storage: f32, or bf16 (nets created with a bf16
-// state), which holds every value rounded to nearest even.  `half` is the
-// net's choice (uniform); indices count values, not bytes.
-__device__ __forceinline__ float state_round(bool half, float x) {
-  return half ? to_f(from_f<bf16_t>(x)) : x;
-}
-__device__ __forceinline__ void state_load8(const float* P, bool half,
-                                            int64_t i, float* f) {
-  if (half)
-    Vec8<bf16_t>::load((const bf16_t*)P + i, f);
-  else
-    load8f(P + i, f);
-}
-__device__ __forceinline__ void state_store8(float* P, bool half, int64_t i,
-                                             const float* f) {
-  if (half)
-    (void)Vec8<bf16_t>::store((bf16_t*)P + i, f);
-  else
-    store8f(P + i, f);
-}
-__device__ __forceinline__ float4 state_load4(const float* P, bool half,
-                                              int64_t i) {
-  if (!half) return *(const float4*)(P + i);
-  const uint2 v = *(const uint2*)((const bf16_t*)P + i);
-  const bf16_t* h = (const bf16_t*)&v;
-  return make_float4(to_f(h[0]), to_f(h[1]), to_f(h[2]), to_f(h[3]));
-}
-__device__ __forceinline__ void state_store4(float* P, bool half, int64_t i,
-                                             float4 f) {
-  if (!half) {
-    *(float4*)(P + i) = f;
-    return;
-  }
-  uint2 v;
-  bf16_t* h = (bf16_t*)&v;
-  h[0] = from_f<bf16_t>(f.x);
-  h[1] = from_f<bf16_t>(f.y);
-  h[2] = from_f<bf16_t>(f.z);
-  h[3] = from_f<bf16_t>(f.w);
-  *(uint2*)((bf16_t*)P + i) = v;
-}
-// The gate slot in use: base + (*par ^ flip) * sz (two slots of one
-// squeeze-excitation layer's per-image gates, chosen by a parity word in
-// device memory so that a captured frame replays with either).
-__device__ __forceinline__ const float* gate_slot(const float* base,
-                                                  const int* par, int64_t sz,
-                                                  int flip) {
-  return base + (int64_t)((*par) ^ flip) * sz;
-}
-__device__ __forceinline__ float state_load1(const float* P, bool half,
-                                             int64_t i) {
-  return half ? to_f(((const bf16_t*)P)[i]) : P[i];
-}
 
 // Reduction stages of a layer that hold real (not padding) columns.
 template <typename T>
@@ -1766,7 +1604,9 @@ __global__ __launch_bounds__(256) void k_split_epi(ConvArgs a) {
   const int64_t tiles_m = (nO + BM - 1) / BM;
   const int tiles_n = (a.cout_p + BN - 1) / BN;
   const int64_t ntiles = tiles_m * tiles_n;
-  const int S = split_count(ntiles, gemm_stages<T>(a), a.split_max);
+  const int S = a.dense
+                    ? a.dense_splits
+                    : split_count(ntiles, gemm_stages<T>(a), a.split_max);
   const int tid = threadIdx.x, cout_p = a.cout_p;
   const int em = tid >> 2, ec = (tid & 3) * 16;
   const T* dskip = (const T*)a.dskip;
@@ -2156,6 +1996,23 @@ static void split_epi_t(hipStream_t s, int grid, const ConvArgs& a) {
     k_split_epi<T, false><<<grid, 256, 0, s>>>(a);
 }
 
+// dense_splits: the dense pass's split count (else 0: the device's).
+static void split_epilogue(const Prof& pf, hipStream_t s, int dtype,
+                           ConvArgs a, int dense_splits) {
+  const int64_t tiles = ((a.capO + kGemmBM - 1) / kGemmBM) *
+                        ((a.cout_p + kGemmBN - 1) / kGemmBN);
+  const int grid = (int)(tiles < 1024 ? tiles : 1024);
+  a.dense_splits = dense_splits;
+  prof_begin(pf, 22 /*ST_K_CONV_SPLIT_EPI*/, s);
+  if (dtype == 0)
+    split_epi_t<float>(s, grid, a);
+  else if (dtype == 1)
+    split_epi_t<_Float16>(s, grid, a);
+  else
+    split_epi_t<bf16_t>(s, grid, a);
+  prof_end(pf, 22, s);
+}
+
 // ------------------------------------------------ dense stem (reference)
 // Dense reference pass of a 7x7 stride-2 convolution over rows of at most
 // four channels (a ResNet stem) with at most 64 output channels.  A tile is
@@ -2419,6 +2276,13 @@ bool launch_conv_gemm(const Prof& pf, hipStream_t s, int dtype,
     prof_end(pf, 7, s);
     return true;
   }
+  if (a.dense && dense_conv_rows(dtype, a)) {
+    prof_begin(pf, 7 /*ST_K_CONV_GEMM*/, s);
+    const int splits = launch_dense_conv(s, dtype, a);
+    prof_end(pf, 7, s);
+    if (splits > 1) split_epilogue(pf, s, dtype, a, splits);
+    return true;
+  }
   if (use_big(dtype, a)) {
     const int64_t halves =
         (a.capO + chunk_tile_step(a.nf) - 1) / chunk_tile_step(a.nf);
@@ -2447,17 +2311,7 @@ bool launch_conv_gemm(const Prof& pf, hipStream_t s, int dtype,
   prof_begin(pf, 7 /*ST_K_CONV_GEMM*/, s);
   fn<<<grid, 256, lds, s>>>(a);
   prof_end(pf, 7, s);
-  if (a.split_max > 1) {
-    const int egrid = (int)(worst < 1024 ? worst : 1024);
-    prof_begin(pf, 22 /*ST_K_CONV_SPLIT_EPI*/, s);
-    if (dtype == 0)
-      split_epi_t<float>(s, egrid, a);
-    else if (dtype == 1)
-      split_epi_t<_Float16>(s, egrid, a);
-    else
-      split_epi_t<bf16_t>(s, egrid, a);
-    prof_end(pf, 22, s);
-  }
+  if (a.split_max > 1) split_epilogue(pf, s, dtype, a, 0);
   return true;
 }
 

@@ -1,0 +1,111 @@
+"""The reference pass's dense convolutions against f64, at the edges of their
+tiles, stage columns and reduction splits, for every tile shape of the rule
+(the tile follows from the output's pixels and channels)."""
+
+import numpy as np
+import pytest
+import torch
+import torch.nn.functional as F
+
+from workloads.nets import LayerSpec, to_storage
+
+pytestmark = pytest.mark.gpu
+
+# (dtype, batch, H, W, c_in, c_out, k, s, p)
+CASES = [
+    # one pixel; fewer pixels or channels than a 64x64 tile; one more
+    ("bf16", 1, 1, 1, 8, 8, 1, 1, 0),
+    ("f16", 1, 7, 9, 64, 64, 3, 1, 1),
+    ("bf16", 1, 5, 13, 72, 72, 1, 1, 0),
+    ("f32", 1, 5, 13, 36, 40, 3, 1, 1),
+    # channels below, at and above a stage's columns; strides; 5x5; no pad
+    ("f16", 2, 17, 11, 24, 56, 3, 2, 1),
+    ("bf16", 1, 20, 23, 128, 24, 3, 1, 0),
+    ("bf16", 1, 31, 33, 16, 80, 5, 2, 2),
+    ("f32", 2, 19, 21, 16, 64, 3, 2, 1),
+    ("f32", 1, 9, 14, 4, 64, 3, 1, 1),
+    ("f16", 1, 33, 31, 40, 64, 1, 2, 0),
+    # split reductions: few tiles, long, ragged last split
+    ("bf16", 1, 6, 11, 512, 136, 3, 1, 1),
+    ("f16", 1, 3, 5, 2048, 72, 1, 1, 0),
+    ("f32", 1, 8, 8, 200, 72, 3, 1, 1),
+    # 128x32, 128x64 (3 and 2 stages) and 128x128 tiles, ragged in pixels
+    # and channels
+    ("bf16", 1, 169, 170, 32, 24, 1, 1, 0),
+    ("f32", 1, 169, 170, 16, 32, 1, 1, 0),
+    ("bf16", 1, 169, 171, 64, 64, 3, 1, 1),
+    ("f32", 1, 171, 169, 8, 56, 3, 1, 1),
+    ("f16", 3, 210, 209, 16, 48, 1, 1, 0),
+    ("bf16", 1, 363, 363, 8, 64, 1, 1, 0),
+    ("bf16", 1, 171, 169, 128, 120, 1, 1, 0),
+    ("f16", 1, 120, 121, 64, 200, 3, 1, 1),
+    ("f32", 1, 121, 120, 24, 136, 1, 1, 0),
+]
+
+
+@pytest.mark.parametrize("act", [0, 2])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_dense_convolution(case, act):
+    from paper_2410_20790_amd import SparseTemNet
+    dtype, n, h, w, cin, cout, k, s, p = case
+    print("dense", case, act, flush=True)
+    rng = np.random.default_rng(7)
+    std = (cin * k * k) ** -0.5
+    L = LayerSpec(src=-1, c_in=cin, c_out=cout, k=(k, k), s=(s, s), p=(p, p),
+                  act=act)
+    L.weight = to_storage(rng.normal(0, std, (cout, cin, k, k)), dtype)
+    L.bias = to_storage(rng.normal(0, 1, (cout,)), dtype)
+    x = to_storage(rng.normal(0, 1, (n, h, w, cin)), dtype)
+    net = SparseTemNet([L], n, h, w, cin, dtype)
+    try:
+        out = net.encode_reference(
+            torch.from_numpy(x).to("cuda", net.tdtype)).cpu().double()
+    finally:
+        net.close()
+    xd = torch.from_numpy(x).double().permute(0, 3, 1, 2)
+    wd, bd = (torch.from_numpy(a).double() for a in (L.weight, L.bias))
+    want = F.conv2d(xd, wd, bd, s, p)
+    # f32 sums of exact products (half) or of rounded ones (f32): at most
+    # one rounding of the running sum per term; |f'| <= 1.1 for SiLU
+    size = F.conv2d(xd.abs(), wd.abs(), bd.abs(), s, p)
+    bound = 1.1 * (2 + cin * k * k) * 2.0 ** -24 * size + 1e-6
+    if act:
+        want = F.silu(want)
+    err = (out.permute(0, 3, 1, 2) - want).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("hw", [(9, 7), (169, 170)])
+def test_dense_residual(dtype, hw):
+    """A residual row added before the activation, on the smallest and a
+    larger tile: every emitted row of the first layer is its rounded
+    activation, so the second layer's sum is known from it."""
+    from paper_2410_20790_amd import SparseTemNet
+    from paper_2410_20790_amd import binding as B
+    h, w = hw
+    rng = np.random.default_rng(11)
+    layers = []
+    for src, cin, res in ((-1, 8, -2), (0, 40, 0)):
+        L = LayerSpec(src=src, c_in=cin, c_out=40, k=(1, 1), s=(1, 1),
+                      p=(0, 0), act=1, residual_src=res)
+        L.weight = to_storage(rng.normal(0, cin ** -0.5, (40, cin, 1, 1)),
+                              dtype)
+        L.bias = to_storage(rng.normal(0, 1, (40,)), dtype)
+        layers.append(L)
+    x = to_storage(rng.normal(0, 1, (1, h, w, 8)), dtype)
+    net = SparseTemNet(layers, 1, h, w, 8, dtype)
+    try:
+        out = net.encode_reference(
+            torch.from_numpy(x).to("cuda", net.tdtype)).cpu().double()
+        p0 = torch.from_numpy(B.st_debug_state(net.handle, 0,
+                                               (1, h, w, 40)))
+    finally:
+        net.close()
+    row = p0.clamp(min=0).to(net.tdtype).double().permute(0, 3, 1, 2)
+    wd, bd = (torch.from_numpy(a).double()
+              for a in (layers[1].weight, layers[1].bias))
+    want = F.relu(F.conv2d(row, wd, bd) + row)
+    size = F.conv2d(row.abs(), wd.abs(), bd.abs()) + row.abs()
+    err = (out.permute(0, 3, 1, 2) - want).abs()
+    assert bool((err <= 44 * 2.0 ** -24 * size + 1e-6).all())
