@@ -282,9 +282,10 @@ struct SeArgs {
   float keep_thr;
   const float* keep_thr_dev;  // in device memory (or NULL: keep_thr)
   const float* yhat;          // residual carry view or NULL
-  float* gout;                // excitation: gates to [N][cp] here instead
-                              // of the new slot (or NULL)
-  // excitation of a chunk's frames in one launch (nfr frames in order,
+  float* gout;                // excitation: gates to [N][cp] here (the last
+                              // frame's to the new slot too) instead of the
+                              // new slot (or NULL)
+  // excitation of a chunk's frames in one pass (nfr frames in order,
   // frame t's partials at part + t * part_stride, its gates at gout +
   // t * gout_stride); nfr 0 or 1: one frame
   int nfr;

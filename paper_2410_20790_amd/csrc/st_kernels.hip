@@ -2657,122 +2657,187 @@ __global__ __launch_bounds__(256) void k_se_squeeze(SeArgs a) {
     a.part[((int64_t)n * a.nchunk + g) * cp + c] = sm[c];
 }
 
-// Excitation of one image per block (1024 threads): the frame's partial
-// sums over the site chunks (Lc lanes per 4-channel column, then the Lc
-// results in lane order) move the f64 channel sums S; the means feed the
-// hidden units (one wave per unit, two units per pass) and the gates
-// (each 4-channel output split over Lg thread groups of the hidden units,
-// then summed in group order).
-constexpr int kSeExciteThreads = 1024;
-__global__ __launch_bounds__(kSeExciteThreads) void k_se_excite(SeArgs a) {
-  constexpr int NT = kSeExciteThreads;
-  extern __shared__ __align__(16) float sm[];  // [cp] means, [mid], [NT] x4
-  float* m = sm;
-  float* z = sm + a.cp;
-  float4* red = (float4*)(sm + a.cp + round_up8(a.mid));
-  const int n = blockIdx.x, cp = a.cp, V4 = cp / 4, t = threadIdx.x;
+// Excitation in two launches.  What bounds it is the chain of dependent
+// steps, each a memory round trip or a barrier, on few blocks; one block per
+// image that did it all, a chunk's frames one after another, took 55 us for
+// the seven diff frames of an EfficientNet-B0 layer at 512x512 (now 16) and
+// 11 us for one frame.  Only the channel sums S depend on the frame before, so the means
+// of all frames come first (k_se_means, 64 channels of one image per block),
+// then every frame's and image's gates at once (k_se_gates).
+//
+// Means: 16 lanes per 4-channel column sum a frame's partials over the site
+// chunks, the lanes' sums are added in lane order and move the f64 sums S
+// frame by frame.  Frame t's means go to the first chunk's row of its
+// partials, which only this block reads.
+constexpr int kSeMeanFrames = 8;  // frames whose partials are held at once
+__global__ __launch_bounds__(256) void k_se_means(SeArgs a) {
+  __shared__ float4 red[kSeMeanFrames][256];
+  __shared__ float tot[kSeMeanFrames][64];
+  const int n = blockIdx.y, cp = a.cp, V4 = cp / 4, tid = threadIdx.x;
+  const int v = blockIdx.x * 16 + (tid & 15), l = tid >> 4;
   const int nfr = a.nfr > 1 ? a.nfr : 1;
-  // frames in order: frame fr + 1 starts from the sums frame fr left
-  for (int fr = 0; fr < nfr; ++fr) {
-    float* s_new = a.gout ? a.gout + fr * a.gout_stride
-                          : const_cast<float*>(gate_slot(a.gates, a.gpar,
-                                                         a.gsz, 1));
-    const int Lc = V4 <= NT ? NT / V4 : 1;
-    const float4* part = (const float4*)(a.part + fr * a.part_stride +
-                                         (int64_t)n * a.nchunk * cp);
-    for (int v0 = 0; v0 < V4; v0 += NT) {
-      const int v = v0 + (Lc > 1 ? t % V4 : t), l = Lc > 1 ? t / V4 : 0;
+  const int c = blockIdx.x * 64 + (tid & 63);
+  double* S = a.S + (int64_t)n * cp + c;
+  double sum = 0.0;
+  if (tid < 64 && c < cp && !a.ref) sum = *S;
+  for (int f0 = 0; f0 < nfr; f0 += kSeMeanFrames) {
+    const int nb = min(kSeMeanFrames, nfr - f0);
+    for (int f = 0; f < nb; ++f) {
+      const float4* part = (const float4*)(a.part +
+                                           (f0 + f) * a.part_stride +
+                                           (int64_t)n * a.nchunk * cp);
       float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (v < V4 && l < Lc) {
-        for (int g = l; g < a.nchunk; g += Lc) {
+      if (v < V4) {
+#pragma unroll 8
+        for (int g = l; g < a.nchunk; g += 16) {
           const float4 q = part[(int64_t)g * V4 + v];
           acc.x += q.x; acc.y += q.y; acc.z += q.z; acc.w += q.w;
         }
       }
-      red[t] = acc;
-      __syncthreads();
-      if (v < V4 && l == 0) {
-        float4 tot = red[t];
-        for (int j = 1; j < Lc; ++j) {
-          const float4 q = red[t + j * V4];
-          tot.x += q.x; tot.y += q.y; tot.z += q.z; tot.w += q.w;
-        }
-        const float tv[4] = {tot.x, tot.y, tot.z, tot.w};
-  #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int c = 4 * v + k;
-          double* S = a.S + (int64_t)n * cp + c;
-          const double sv = (a.ref ? 0.0 : *S) + (double)tv[k];
-          *S = sv;
-          m[c] = (float)(sv / (double)a.hw);
-        }
-      }
-      __syncthreads();
-    }
-    // hidden units z = silu(w1 . m + b1)
-    const int lane = t & 63, wave = t >> 6, nw = NT / 64;
-    const float4* m4 = (const float4*)m;
-    for (int j0 = wave; j0 < a.mid; j0 += 2 * nw) {
-      const int j1 = j0 + nw;
-      const float4* w0 = (const float4*)(a.w1 + (int64_t)j0 * cp);
-      const float4* w1 = (const float4*)(a.w1 + (int64_t)(j1 < a.mid ? j1 : j0)
-                                         * cp);
-      float d0 = 0.f, d1 = 0.f;
-  #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int v = lane + 64 * i;
-        if (v < V4) {
-          const float4 x = m4[v], p = w0[v], q = w1[v];
-          d0 += p.x * x.x + p.y * x.y + p.z * x.z + p.w * x.w;
-          d1 += q.x * x.x + q.y * x.y + q.z * x.z + q.w * x.w;
-        }
-      }
-  #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        d0 += __shfl_xor(d0, o, 64);
-        d1 += __shfl_xor(d1, o, 64);
-      }
-      if (lane == 0) {
-        z[j0] = act_f(d0 + a.b1[j0], 2);
-        if (j1 < a.mid) z[j1] = act_f(d1 + a.b1[j1], 2);
-      }
+      red[f][tid] = acc;
     }
     __syncthreads();
-    // gates: output vector v, hidden units split over Lg groups
-    const int Lg = V4 <= NT ? NT / V4 : 1;
-    for (int v0 = 0; v0 < V4; v0 += NT) {
-      const int v = v0 + (Lg > 1 ? t % V4 : t), l = Lg > 1 ? t / V4 : 0;
-      float4 e = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (v < V4 && l < Lg) {
-        const float4* w = (const float4*)a.w2t + v;
-  #pragma unroll 4
-        for (int j = l; j < a.mid; j += Lg) {
-          const float4 q = w[(int64_t)j * V4];
-          const float zj = z[j];
-          e.x += q.x * zj; e.y += q.y * zj; e.z += q.z * zj; e.w += q.w * zj;
-        }
+    for (int i = tid; i < nb * 64; i += 256) {
+      const int f = i >> 6, k = i & 63;
+      const float* r = (const float*)red[f] + k;
+      float s = r[0];
+#pragma unroll
+      for (int j = 1; j < 16; ++j) s += r[64 * j];
+      tot[f][k] = s;
+    }
+    __syncthreads();
+    if (tid < 64 && c < cp)
+      for (int f = 0; f < nb; ++f) {
+        sum += (double)tot[f][tid];
+        a.part[(f0 + f) * a.part_stride + (int64_t)n * a.nchunk * cp + c] =
+            (float)(sum / (double)a.hw);
       }
-      red[t] = e;
-      __syncthreads();
-      if (v < V4 && l == 0) {
-        float4 tot = ((const float4*)a.b2)[v];
-        for (int j = 0; j < Lg; ++j) {
-          const float4 q = red[t + j * V4];
-          tot.x += q.x; tot.y += q.y; tot.z += q.z; tot.w += q.w;
-        }
-        const float ev[4] = {tot.x, tot.y, tot.z, tot.w};
-  #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int c = 4 * v + k;
-          s_new[(int64_t)n * cp + c] =
-              c < a.c ? 1.f / (1.f + expf(-ev[k])) : 0.f;
-        }
+    // (the next turn writes red before its first barrier and tot after it)
+  }
+  if (tid < 64 && c < cp) *S = sum;
+}
+
+// Gates of image blockIdx.x in frame blockIdx.y from its means: the hidden
+// units (one wave per unit, two units per pass; the first pass's weights are
+// requested before the means), then the gates (each 4-channel output split
+// over Lg thread groups of the hidden units, summed in group order).
+constexpr int kSeExciteThreads = 1024;
+__global__ __launch_bounds__(kSeExciteThreads) void k_se_gates(SeArgs a) {
+  constexpr int NT = kSeExciteThreads, NW = NT / 64;
+  extern __shared__ __align__(16) float sm[];  // [cp] means, [mid], [NT] x4
+  float* m = sm;
+  float* z = sm + a.cp;
+  float4* red = (float4*)(sm + a.cp + round_up8(a.mid));
+  const int n = blockIdx.x, fr = blockIdx.y, cp = a.cp, V4 = cp / 4;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  float4 p[8], q[8];
+  auto request = [&](int j0) {
+    const int j1 = j0 + NW;
+    const float4* w0 = (const float4*)(a.w1 + (int64_t)j0 * cp);
+    const float4* w1 =
+        (const float4*)(a.w1 + (int64_t)(j1 < a.mid ? j1 : j0) * cp);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int v = lane + 64 * i;
+      p[i] = q[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (v < V4) {
+        p[i] = w0[v];
+        q[i] = w1[v];
       }
-      __syncthreads();
+    }
+  };
+  if (wave < a.mid) request(wave);
+  const float* mean = a.part + fr * a.part_stride + (int64_t)n * a.nchunk * cp;
+  for (int c = t; c < cp; c += NT) m[c] = mean[c];
+  __syncthreads();
+  // hidden units z = silu(w1 . m + b1)
+  const float4* m4 = (const float4*)m;
+  for (int j0 = wave; j0 < a.mid; j0 += 2 * NW) {
+    const int j1 = j0 + NW;
+    if (j0 != wave) request(j0);
+    float d0 = 0.f, d1 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int v = lane + 64 * i;
+      if (v < V4) {
+        const float4 x = m4[v];
+        d0 += p[i].x * x.x + p[i].y * x.y + p[i].z * x.z + p[i].w * x.w;
+        d1 += q[i].x * x.x + q[i].y * x.y + q[i].z * x.z + q[i].w * x.w;
+      }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      d0 += __shfl_xor(d0, o, 64);
+      d1 += __shfl_xor(d1, o, 64);
+    }
+    if (lane == 0) {
+      z[j0] = act_f(d0 + a.b1[j0], 2);
+      if (j1 < a.mid) z[j1] = act_f(d1 + a.b1[j1], 2);
+    }
+  }
+  // gates: output vector v, hidden units split over Lg groups
+  float* s_new = const_cast<float*>(gate_slot(a.gates, a.gpar, a.gsz, 1));
+  float* s_fr = a.gout ? a.gout + fr * a.gout_stride : s_new;
+  // a chunk's last gates are the next chunk's previous ones
+  const bool both = a.gout && fr + 1 == (int)gridDim.y;
+  const int Lg = V4 <= NT ? NT / V4 : 1;
+  for (int v0 = 0; v0 < V4; v0 += NT) {
+    const int v = v0 + (Lg > 1 ? t % V4 : t), l = Lg > 1 ? t / V4 : 0;
+    // the first eight hidden units' weights arrive while the block waits
+    float4 w[8];
+    const float4* wv = (const float4*)a.w2t + v;
+    const bool in = v < V4 && l < Lg;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      w[i] = in && l + i * Lg < a.mid ? wv[(int64_t)(l + i * Lg) * V4]
+                                      : make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();  // the hidden units; the last turn's red is read
+    float4 e = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (in) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int j = l + i * Lg;
+        if (j >= a.mid) break;
+        const float zj = z[j];
+        e.x += w[i].x * zj; e.y += w[i].y * zj;
+        e.z += w[i].z * zj; e.w += w[i].w * zj;
+      }
+#pragma unroll 4
+      for (int j = l + 8 * Lg; j < a.mid; j += Lg) {
+        const float4 x = wv[(int64_t)j * V4];
+        const float zj = z[j];
+        e.x += x.x * zj; e.y += x.y * zj; e.z += x.z * zj; e.w += x.w * zj;
+      }
+    }
+    red[t] = e;
+    __syncthreads();
+    if (v < V4 && l == 0) {
+      float4 tot = ((const float4*)a.b2)[v];
+      for (int j = 0; j < Lg; ++j) {
+        const float4 x = red[t + j * V4];
+        tot.x += x.x; tot.y += x.y; tot.z += x.z; tot.w += x.w;
+      }
+      const float ev[4] = {tot.x, tot.y, tot.z, tot.w};
+      float4 gv;
+      float* ge = (float*)&gv;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        ge[k] = 4 * v + k < a.c ? 1.f / (1.f + expf(-ev[k])) : 0.f;
+      *(float4*)(s_fr + (int64_t)n * cp + 4 * v) = gv;
+      if (both) *(float4*)(s_new + (int64_t)n * cp + 4 * v) = gv;
     }
   }
 }
 
+static void se_excite(const Prof& pf, hipStream_t s, const SeArgs& a) {
+  prof_begin(pf, 20 /*ST_K_SE_EXCITE*/, s);
+  k_se_means<<<dim3((a.cp + 63) / 64, a.N), 256, 0, s>>>(a);
+  k_se_gates<<<dim3(a.N, a.nfr > 1 ? a.nfr : 1), kSeExciteThreads,
+               sizeof(float) * (a.cp + round_up8(a.mid) +
+                                4 * kSeExciteThreads),
+               s>>>(a);
+  prof_end(pf, 20, s);
+}
 
 template <typename T, int TPS>
 __global__ __launch_bounds__(256) void k_se_emit(SeArgs a) {
@@ -2838,12 +2903,7 @@ static void se_t(const Prof& pf, hipStream_t s, int dtype, const SeArgs& a) {
   prof_begin(pf, 19 /*ST_K_SE_SQUEEZE*/, s);
   k_se_squeeze<TPS><<<dim3(a.nchunk, a.N), 256, 0, s>>>(a);
   prof_end(pf, 19, s);
-  prof_begin(pf, 20 /*ST_K_SE_EXCITE*/, s);
-  k_se_excite<<<a.N, kSeExciteThreads,
-                sizeof(float) * (a.cp + round_up8(a.mid) +
-                                 4 * kSeExciteThreads),
-                s>>>(a);
-  prof_end(pf, 20, s);
+  se_excite(pf, s, a);
   constexpr int R = 256 / TPS;
   const int blocks = (int)((a.npix + R - 1) / R);
   prof_begin(pf, 21 /*ST_K_SE_EMIT*/, s);
@@ -3000,23 +3060,12 @@ __global__ __launch_bounds__(256) void k_chunk_se_emit(ChunkSeArgs a) {
     *a.cnt_rows = (u64)(a.npix * a.nf);
 }
 
-// The chunk's last gates become the new slot's (the slots flip after the
-// chunk).
-__global__ void k_gate_copy(const float* src, float* slots, const int* gpar,
-                            int64_t gsz, int64_t n) {
-  float* dst = const_cast<float*>(gate_slot(slots, gpar, gsz, 1));
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * 256)
-    dst[i] = src[i];
-}
-
 template <int TPS>
 static void chunk_se_t(const Prof& pf, hipStream_t s, int dtype,
                        const ChunkSeArgs& c, const SeArgs& ex) {
   prof_begin(pf, 19 /*ST_K_SE_SQUEEZE*/, s);
   k_chunk_se_squeeze<TPS><<<dim3(c.nchunk, c.N, c.nf), 256, 0, s>>>(c);
   prof_end(pf, 19, s);
-  prof_begin(pf, 20 /*ST_K_SE_EXCITE*/, s);
   SeArgs e = ex;
   e.part = c.part;
   e.gout = c.gates;
@@ -3024,11 +3073,7 @@ static void chunk_se_t(const Prof& pf, hipStream_t s, int dtype,
   e.part_stride = (int64_t)c.N * c.nchunk * c.cp;
   e.gout_stride = (int64_t)c.N * c.cp;
   e.ref = 0;
-  k_se_excite<<<c.N, kSeExciteThreads,
-                sizeof(float) * (c.cp + round_up8(e.mid) +
-                                 4 * kSeExciteThreads),
-                s>>>(e);
-  prof_end(pf, 20, s);
+  se_excite(pf, s, e);
   constexpr int R = 256 / TPS;
   const int blocks = (int)((c.npix + R - 1) / R);
   prof_begin(pf, 21 /*ST_K_SE_EMIT*/, s);
@@ -3038,9 +3083,6 @@ static void chunk_se_t(const Prof& pf, hipStream_t s, int dtype,
     k_chunk_se_emit<_Float16, TPS><<<blocks, 256, 0, s>>>(c);
   else
     k_chunk_se_emit<bf16_t, TPS><<<blocks, 256, 0, s>>>(c);
-  const int64_t ng = (int64_t)c.N * c.cp;
-  k_gate_copy<<<grid_for(ng, 256), 256, 0, s>>>(
-      c.gates + (int64_t)(c.nf - 1) * ng, c.slots, c.gpar, c.gsz, ng);
   prof_end(pf, 21, s);
 }
 
