@@ -119,6 +119,26 @@ __device__ __forceinline__ void store8f(float* p, const float* f) {
   *(float4*)(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
 }
 
+// The values a row of type T holds after rounding, as f32 (the view that a
+// residual-carry reference frame starts from its emitted rows).
+template <typename T>
+__device__ __forceinline__ void store8f_rounded(float* p, const float* f) {
+  float r[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) r[e] = to_f(from_f<T>(f[e]));
+  store8f(p, r);
+}
+
+// 8-channel vectors of a site that adjacent threads of a 256-thread block
+// take in the dense pass's per-site kernels: all of them, or the largest
+// divisor between 16 and 64 (no thread idle), or 64.
+inline int octets_per_block(int v) {
+  if (v <= 64) return v;
+  for (int t = 64; t >= 16; --t)
+    if (v % t == 0) return t;
+  return 64;
+}
+
 // Pre-activation state storage: f32, or bf16 (nets created with a bf16
 // state), which holds every value rounded to nearest even.  `half` is the
 // net's choice (uniform); indices count values, not bytes.

@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -62,7 +63,11 @@ void prof_end(const Prof& p, int cls, hipStream_t s) {
 // only that address is used.  A generation count per device records which
 // net bound the array last; a net whose binding was taken over refuses to
 // run.
-static __device__ __align__(256) char scratch[ST_STATIC_WORKSPACE_BYTES];
+// (kStaticTables: room for the reference tables of nets that may use the
+// whole limit besides, see st_net::static_extra.)
+constexpr size_t kStaticTables = 256 << 10;
+static __device__ __align__(256) char
+    scratch[ST_STATIC_WORKSPACE_BYTES + kStaticTables];
 
 namespace {
 
@@ -213,9 +218,39 @@ ConsList consumers_of(st_net* net, int t, bool list_pass = false) {
 
 IbstArgs ibst_args(st_net* net);
 
+// What every launch of layer i's squeeze-excitation shares.
+SeArgs se_args(st_net* net, int i) {
+  const WS ws{net->ws};
+  const LayerPlan& L = net->layers[i];
+  SeArgs a{};
+  a.p16 = net->bf16_state ? 1 : 0;
+  a.P = ws.at<float>(L.off_P);
+  a.part = ws.at<float>(L.off_separt);
+  a.S = ws.at<double>(L.off_sesum);
+  a.w1 = ws.at<float>(L.off_sew1);
+  a.b1 = ws.at<float>(L.off_seb1);
+  a.w2t = ws.at<float>(L.off_sew2);
+  a.b2 = ws.at<float>(L.off_seb2);
+  a.gates = ws.at<float>(L.off_ses);
+  a.gpar = ws.at<int>(net->off_se_par);
+  a.gsz = (int64_t)net->N * L.cout_p;
+  a.dout = ws.at<char>(net->tensors[i + 1].off_rows);
+  a.npix = L.conv_grid;
+  a.hw = (int64_t)L.Ho * L.Wo;
+  a.N = net->N;
+  a.cp = L.cout_p;
+  a.c = L.d.c_out;
+  a.mid = L.se_mid;
+  a.act = L.d.act;
+  a.chunk = L.se_chunk;
+  a.nchunk = L.se_nchunk;
+  a.tps = L.se_tps;
+  return a;
+}
+
 // thr_dev: this layer's emitted-tensor threshold in device memory (online
 // adjustment), or NULL to use thr.
-bool run_layer(st_net* net, int i, bool ref, float thr, const float* thr_dev,
+bool run_layer(st_net* net, int i, float thr, const float* thr_dev,
                hipStream_t s) {
   const WS ws{net->ws};
   const LayerPlan& L = net->layers[i];
@@ -231,9 +266,9 @@ bool run_layer(st_net* net, int i, bool ref, float thr, const float* thr_dev,
   u64* cO = cnt + L.cnt_O;
   u64* cpairs = cnt + L.cnt_pairs;
   uint32_t* rowmax_out = ws.at<uint32_t>(out.off_rowmax);
-  // frozen squeeze-excitation in a diff frame: a state-mode layer whose
-  // emitted values are scaled by the reference frame's gates
-  const bool frozen = L.se && net->frozen_se && !ref;
+  // frozen squeeze-excitation: a state-mode layer whose emitted values are
+  // scaled by the reference frame's gates
+  const bool frozen = L.se && net->frozen_se;
   // pooled and (exact) squeeze-excitation layers emit rows of their own
   // (pooled sites / every site), not the affected conv outputs
   const bool own_rows = L.pool || (L.se && !frozen);
@@ -284,7 +319,6 @@ bool run_layer(st_net* net, int i, bool ref, float thr, const float* thr_dev,
   }
   a.mode = frozen ? kModeState : L.mode;
   a.act = d.act;
-  a.ref = ref ? 1 : 0;
   if (frozen) {
     a.gate = ws.at<float>(L.off_ses);
     a.gpar = ws.at<int>(net->off_se_par);
@@ -329,43 +363,19 @@ bool run_layer(st_net* net, int i, bool ref, float thr, const float* thr_dev,
     pa.rowmax = rowmax_out;
     pa.cp = L.cout_p;
     pa.act = d.act;
-    pa.ref = ref ? 1 : 0;
     pa.yhat = net->carry ? ws.at<float>(L.off_yhat) : nullptr;
     launch_pool_emit(pf, s, net->dtype, pa);
     launch_commit(pf, s, O, cO, L.conv_grid, ws.at<float>(L.off_P),
-                  ws.at<float>(L.off_dP), L.cout_p, ref ? 1 : 0);
+                  ws.at<float>(L.off_dP), L.cout_p);
   }
   if (L.se && !frozen) {
-    SeArgs sa{};
-    sa.p16 = net->bf16_state ? 1 : 0;
-    sa.P = ws.at<float>(L.off_P);
+    SeArgs sa = se_args(net, i);
     sa.dP = ws.at<float>(L.off_dP);
     sa.Mo = Mo;
-    sa.part = ws.at<float>(L.off_separt);
-    sa.S = ws.at<double>(L.off_sesum);
-    sa.w1 = ws.at<float>(L.off_sew1);
-    sa.b1 = ws.at<float>(L.off_seb1);
-    sa.w2t = ws.at<float>(L.off_sew2);
-    sa.b2 = ws.at<float>(L.off_seb2);
-    sa.gates = ws.at<float>(L.off_ses);
-    sa.gpar = ws.at<int>(net->off_se_par);
-    sa.gsz = (int64_t)net->N * L.cout_p;
-    sa.dout = ws.at<char>(out.off_rows);
     sa.rowmax = rowmax_out;
     sa.rowpix = ws.at<int>(out.off_rowpix);
     sa.map = ws.at<int>(out.off_map);
     sa.cnt_rows = cnt + out.cnt_rows;
-    sa.npix = L.conv_grid;
-    sa.hw = (int64_t)L.Ho * L.Wo;
-    sa.tps = L.se_tps;
-    sa.N = net->N;
-    sa.cp = L.cout_p;
-    sa.c = d.c_out;
-    sa.mid = L.se_mid;
-    sa.act = d.act;
-    sa.ref = ref ? 1 : 0;
-    sa.chunk = L.se_chunk;
-    sa.nchunk = L.se_nchunk;
     sa.keep_thr = thr;
     sa.keep_thr_dev = thr_dev;
     sa.yhat = net->carry ? ws.at<float>(L.off_yhat) : nullptr;
@@ -396,15 +406,15 @@ bool run_layer(st_net* net, int i, bool ref, float thr, const float* thr_dev,
   return true;
 }
 
-// The reference frame keeps every pixel (threshold -1 everywhere), so the
-// frame-by-frame pass would compact every tensor into its pixels in order.
-// For nets without squeeze-excitation or residual carry it runs dense
-// instead: each tensor's rows are its pixels, the convolutions take their
-// neighbours from the geometry, and no list, map or rulebook is built.  It
-// leaves what the frame-by-frame reference pass leaves for the diff frames
-// and the queries: X_hat, every state, the emitted rows, the kept lists
-// (identities) and the counters (every row kept, the dense pair counts).
-static st_status encode_dense_ref(st_net* net, const void* frame, float* out,
+// The reference frame keeps every pixel, so it runs dense: each tensor's rows
+// are its pixels, the convolutions take their neighbours from the geometry,
+// and no list, map or rulebook is built.  It leaves what a diff frame with
+// every pixel changed would leave for the diff frames and the queries: X_hat,
+// every state, squeeze-excitation sums and gates, the emitted rows (residual
+// carry: the views, which start as the rows), the kept lists (identities) and
+// the counters (every row kept, the dense pair counts); the affected lists
+// and rulebooks, which follow from the geometry, are made by the queries.
+static st_status encode_reference(st_net* net, const void* frame, float* out,
                                   hipStream_t s) {
   const WS ws{net->ws};
   u64* cnt = ws.at<u64>(net->off_cnt);
@@ -425,8 +435,12 @@ static st_status encode_dense_ref(st_net* net, const void* frame, float* out,
     const TensorPlan& in = net->tensors[d.src + 1];
     TensorPlan& outT = net->tensors[i + 1];
     const Prof pfl{net, i};
-    // a pooled layer's rows are its pool's; the output layer's go nowhere
-    const bool no_rows = L.pool || i == nl - 1;
+    // a pooled or squeeze-excitation layer's rows come after it; the output
+    // layer's are no layer's input (residual carry's view starts as them;
+    // nets with squeeze-excitation keep them for the queries)
+    const bool no_rows = L.pool || L.se ||
+                         (i == nl - 1 && !net->carry && !net->has_se);
+    float* ynew = net->carry ? ws.at<float>(L.off_yhat) : nullptr;
     ConvArgs a{};
     a.p16 = net->bf16_state ? 1 : 0;
     a.din = ws.at<char>(in.off_rows);
@@ -451,21 +465,28 @@ static st_status encode_dense_ref(st_net* net, const void* frame, float* out,
     a.mode = no_rows ? kModeStateOnly
                      : (L.stateful ? kModeState : kModeLinear);
     a.act = d.act;
-    a.ref = 1;
-    a.keep_thr = -1.f;
+    a.ynew = no_rows ? nullptr : ynew;
     a.zero = ws.at<char>(net->off_zero);
     a.part = ws.at<float>(net->off_part);
     a.split_max = L.split_max;
     a.dense = 1;
     a.g = conv_geo(L);
-    if (L.dw)
+    if (L.dw && dense_dw_takes(a))
+      launch_dense_dw(pfl, s, net->dtype, a, net->N);
+    else if (L.dw)
       launch_conv_dw(pfl, s, net->dtype, a);
     else if (!launch_conv_gemm(pfl, s, net->dtype, a))
       return fail(net, ST_ERR_HIP, "internal: GEMM launch arguments");
     if (L.pool)
       launch_pool_dense(pfl, s, net->dtype, ws.at<float>(L.off_P), a.p16,
-                        ws.at<char>(outT.off_rows), pool_geo(L), L.cout_p,
-                        d.act, outT.grid);
+                        ws.at<char>(outT.off_rows), ynew, pool_geo(L),
+                        L.cout_p, d.act, outT.grid);
+    if (L.se) {
+      SeArgs sa = se_args(net, i);
+      sa.ref = 1;
+      sa.ynew = ynew;
+      launch_se(pfl, s, net->dtype, sa);
+    }
     outT.last_thr = -1.f;
   }
   if (out) {
@@ -474,12 +495,18 @@ static st_status encode_dense_ref(st_net* net, const void* frame, float* out,
                                              1, 1, 0, 0};
     launch_output(Prof{net, nl - 1}, s, ws.at<float>(L.off_P),
                   net->bf16_state ? 1 : 0, L.cout_p, L.d.c_out, net->N, g,
-                  L.pool ? 1 : 0, L.d.act, nullptr,
+                  L.pool ? 1 : 0, L.d.act,
+                  L.se ? ws.at<float>(L.off_ses) : nullptr,
                   ws.at<int>(net->off_se_par), 1, out);
   }
+  // the gates just computed become the previous frame's (a parity word in
+  // device memory, so that a captured frame replays correctly)
+  if (net->has_se) launch_flip_parity(s, ws.at<int>(net->off_se_par));
   launch_iota_lists(pf, s, ws.at<IotaEntry>(net->off_iota), net->n_iota,
                     net->ws, net->max_grid);
-  launch_copy_u64(s, cnt, ws.at<u64>(net->off_refcnt), net->n_counters);
+  launch_ref_counters(s, cnt, ws.at<u64>(net->off_refcnt), net->n_counters,
+                      ws.at<int>(net->off_se_par) + 1);
+  // online adjustment: every cycle_refs-th reference frame starts a new cycle
   if (net->ibst_on && net->ibst_refs++ % net->ibst_cycle_refs == 0)
     launch_ibst_restart(s, ibst_args(net));
   if (R && R->n_hist < R->max_frames) {
@@ -492,13 +519,12 @@ static st_status encode_dense_ref(st_net* net, const void* frame, float* out,
   return hip_check(net, "st_encode_reference");
 }
 
-// thr: host thresholds (ignored for the reference frame), or NULL for the
-// thresholds of the online adjustment in device memory.
+// thr: host thresholds, or NULL for those of the online adjustment in device
+// memory.
 st_status encode(st_net* net, const void* frame, const float* thr, float* out,
-                 hipStream_t s, bool ref) {
-  if (ref && net->dense_ref) return encode_dense_ref(net, frame, out, s);
+                 hipStream_t s) {
   const float* thr_dev =
-      (!ref && !thr) ? WS{net->ws}.at<float>(net->off_ibst_thr) : nullptr;
+      thr ? nullptr : WS{net->ws}.at<float>(net->off_ibst_thr);
   const WS ws{net->ws};
   u64* cnt = ws.at<u64>(net->off_cnt);
   net->last_nf = 1;
@@ -507,19 +533,11 @@ st_status encode(st_net* net, const void* frame, const float* thr, float* out,
   if (R) ++R->frame;
   (void)hipGetLastError();  // clear any stale error
 
-  launch_reset(pf, s, cnt, net->n_counters,
-               ws.at<uint32_t>(net->off_tiles));
+  launch_reset(pf, s, cnt, net->n_counters, ws.at<uint32_t>(net->off_tiles),
+               ws.at<int>(net->off_se_par) + 1);
   net->cpar = 0;
-  // residual carry: the reference frame's rows (every site) become the
-  // consumers' whole view
-  if (ref && net->carry)
-    for (const LayerPlan& L : net->layers)
-      launch_fill_u32(s, ws.at<float>(L.off_yhat),
-                      net->tensors[&L - net->layers.data() + 1].grid *
-                          L.cout_p,
-                      0u);
   TensorPlan& T0 = net->tensors[0];
-  const float thr0 = ref ? -1.f : thr_dev ? 0.f : thr[0];
+  const float thr0 = thr_dev ? 0.f : thr[0];
   ScanArgs sa{};
   sa.x = frame;
   sa.xhat = ws.at<char>(net->off_xhat);
@@ -528,7 +546,6 @@ st_status encode(st_net* net, const void* frame, const float* thr, float* out,
   sa.npix = T0.grid;
   sa.thr = thr0;
   sa.thr_dev = thr_dev;
-  sa.ref = ref ? 1 : 0;
   sa.rows = ws.at<char>(T0.off_rows);
   sa.rowpix = ws.at<int>(T0.off_rowpix);
   sa.act = ws.at<int>(T0.off_act);
@@ -541,7 +558,7 @@ st_status encode(st_net* net, const void* frame, const float* thr, float* out,
   T0.last_thr = thr0;
   const int nl = (int)net->layers.size();
   for (int i = 0; i < nl; ++i)
-    if (!run_layer(net, i, ref, ref ? -1.f : thr_dev ? 0.f : thr[i + 1],
+    if (!run_layer(net, i, thr_dev ? 0.f : thr[i + 1],
                    thr_dev ? thr_dev + i + 1 : nullptr, s))
       return fail(net, ST_ERR_HIP, "internal: GEMM launch arguments");
 
@@ -555,20 +572,16 @@ st_status encode(st_net* net, const void* frame, const float* thr, float* out,
                   net->bf16_state ? 1 : 0, L.cout_p, L.d.c_out, net->N, g,
                   L.pool ? 1 : 0, L.d.act,
                   L.se ? ws.at<float>(L.off_ses) : nullptr,
-                  ws.at<int>(net->off_se_par),
-                  (ref || !net->frozen_se) ? 1 : 0, out);
+                  ws.at<int>(net->off_se_par), net->frozen_se ? 0 : 1, out);
   }
   // the gates just computed become the previous frame's (a parity word in
   // device memory, so that a captured frame replays correctly)
-  if (net->has_se && (ref || !net->frozen_se))
+  if (net->has_se && !net->frozen_se)
     launch_flip_parity(s, ws.at<int>(net->off_se_par));
   launch_cleanup(pf, s, ws.at<CleanEntry>(net->off_cleanup), net->n_cleanup,
                  net->ws, cnt, net->max_grid);
-  // online adjustment: every cycle_refs-th reference frame starts a new
-  // cycle; after a diff frame encoded with the device thresholds, one
-  // bisection step
-  if (net->ibst_on && ref && net->ibst_refs++ % net->ibst_cycle_refs == 0)
-    launch_ibst_restart(s, ibst_args(net));
+  // online adjustment: after a diff frame encoded with the device
+  // thresholds, one bisection step
   if (thr_dev) launch_ibst_step(s, cnt, 1, ibst_args(net));
   if (R && R->n_hist < R->max_frames) {
     (void)hipMemcpyAsync(R->hist + (size_t)R->n_hist * net->n_counters, cnt,
@@ -577,7 +590,7 @@ st_status encode(st_net* net, const void* frame, const float* thr, float* out,
     ++R->n_hist;
   }
   net->last_stream = (void*)s;
-  return hip_check(net, ref ? "st_encode_reference" : "st_encode_diff");
+  return hip_check(net, "st_encode_diff");
 }
 
 // ---- chunk mode: the frames of a chunk as items (frame t's sites after
@@ -704,7 +717,6 @@ bool run_layer_chunk(st_net* net, int i, int nf, float thr,
     a.mskip = ws.at<int>(R.off_map);
   }
   a.act = d.act;
-  a.ref = 0;
   a.keep_thr = thr;
   a.keep_thr_dev = thr_dev;
   a.zero = ws.at<char>(net->off_zero);
@@ -776,22 +788,7 @@ bool run_layer_chunk(st_net* net, int i, int nf, float thr,
     c.chunk = L.se_chunk;
     c.nchunk = L.se_nchunk;
     c.tps = L.se_tps;
-    SeArgs ex{};
-    ex.S = ws.at<double>(L.off_sesum);
-    ex.w1 = ws.at<float>(L.off_sew1);
-    ex.b1 = ws.at<float>(L.off_seb1);
-    ex.w2t = ws.at<float>(L.off_sew2);
-    ex.b2 = ws.at<float>(L.off_seb2);
-    ex.gates = c.slots;
-    ex.gpar = c.gpar;
-    ex.gsz = c.gsz;
-    ex.hw = c.hw;
-    ex.N = net->N;
-    ex.cp = L.cout_p;
-    ex.c = d.c_out;
-    ex.mid = L.se_mid;
-    ex.nchunk = L.se_nchunk;
-    launch_chunk_se(pf, s, net->dtype, c, ex);
+    launch_chunk_se(pf, s, net->dtype, c, se_args(net, i));
     launch_chunk_commit(pf, s, c.p16, ws.at<float>(L.off_P), cdp, O, cO,
                         ws.at<uint32_t>(net->off_chunk_aff), citems,
                         L.conv_grid, L.cout_p);
@@ -869,8 +866,8 @@ st_status encode_chunk(st_net* net, const void* frames, int nf,
   (void)hipGetLastError();
   net->last_nf = nf;
 
-  launch_reset(pf, s, cnt, net->n_counters,
-               ws.at<uint32_t>(net->off_tiles));
+  launch_reset(pf, s, cnt, net->n_counters, ws.at<uint32_t>(net->off_tiles),
+               ws.at<int>(net->off_se_par) + 1);
   net->cpar = 0;
   TensorPlan& T0 = net->tensors[0];
   ChunkScanArgs sa{};
@@ -1017,7 +1014,7 @@ extern "C" st_status st_bind_workspace(st_net* net, void* dev_ptr,
   static thread_local std::vector<u64> keep_cnt;
   static thread_local std::vector<IotaEntry> keep_iota;
   static_assert(sizeof(IotaEntry) == 16, "iota entry layout");
-  if (net->dense_ref && e == hipSuccess) {
+  if (e == hipSuccess) {
     keep_cnt.assign(net->n_counters, 0);
     keep_iota.clear();
     for (const TensorPlan& T : net->tensors) {
@@ -1048,7 +1045,8 @@ extern "C" st_status st_bind_workspace(st_net* net, void* dev_ptr,
 
 extern "C" st_status st_bind_workspace_static(st_net* net, void* stream) {
   if (!net) return fail(nullptr, ST_ERR_INVALID_ARG, "net is NULL");
-  if (net->ws_bytes > (size_t)ST_STATIC_WORKSPACE_BYTES)
+  if (net->ws_bytes - net->static_extra > (size_t)ST_STATIC_WORKSPACE_BYTES ||
+      net->static_extra > kStaticTables)
     return fail(net, ST_ERR_WORKSPACE,
                 "the net needs " + std::to_string(net->ws_bytes) +
                     " workspace bytes; the static workspace holds " +
@@ -1086,8 +1084,8 @@ extern "C" st_status st_bind_workspace_static(st_net* net, void* stream) {
   }
   // the plain binding initialises every byte the net uses (zeros, empty
   // pixel maps, repacked weights), whatever the last binding left
-  const st_status st = st_bind_workspace(net, ptr,
-                                         ST_STATIC_WORKSPACE_BYTES, stream);
+  const st_status st = st_bind_workspace(
+      net, ptr, ST_STATIC_WORKSPACE_BYTES + kStaticTables, stream);
   if (st != ST_OK) return st;
   net->static_dev = dev;
   net->static_gen = gen;
@@ -1099,7 +1097,7 @@ extern "C" st_status st_encode_reference(st_net* net, const void* frame,
   if (!net) return fail(nullptr, ST_ERR_INVALID_ARG, "net is NULL");
   if (const st_status w = need_ws(net); w != ST_OK) return w;
   if (!frame) return fail(net, ST_ERR_INVALID_ARG, "frame is NULL");
-  st_status s = encode(net, frame, nullptr, out, (hipStream_t)stream, true);
+  st_status s = encode_reference(net, frame, out, (hipStream_t)stream);
   if (s == ST_OK) net->have_ref = true;
   return s;
 }
@@ -1163,7 +1161,7 @@ extern "C" st_status st_encode_diff(st_net* net, const void* frame,
     if (std::isnan(thr[i]))
       return fail(net, ST_ERR_INVALID_ARG,
                   "threshold " + std::to_string(i) + " is NaN");
-  return encode(net, frame, thr, out, (hipStream_t)stream, false);
+  return encode(net, frame, thr, out, (hipStream_t)stream);
 }
 
 extern "C" st_status st_set_threshold_control(st_net* net,
@@ -1239,7 +1237,7 @@ extern "C" st_status st_encode_diff_adaptive(st_net* net, const void* frame,
     return fail(net, ST_ERR_STATE,
                 "st_encode_diff_adaptive before st_encode_reference");
   if (!frame) return fail(net, ST_ERR_INVALID_ARG, "NULL frame");
-  return encode(net, frame, nullptr, out, (hipStream_t)stream, false);
+  return encode(net, frame, nullptr, out, (hipStream_t)stream);
 }
 
 extern "C" st_status st_get_thresholds(st_net* net, float* thr) {
@@ -1336,7 +1334,12 @@ extern "C" st_status st_debug_candidates(st_net* net, int32_t layer,
   if (st != ST_OK) return st;
   *n = (int64_t)k;
   const int64_t m = std::min<int64_t>(k, cap);
-  if (pix) {
+  int last_ref = 0;
+  if ((st = d2h(net, &last_ref, ws.at<int>(net->off_se_par) + 1, 1)) != ST_OK)
+    return st;
+  if (pix && last_ref) {
+    std::iota(pix, pix + m, 0);  // a reference frame's rows are its pixels
+  } else if (pix) {
     st = d2h(net, pix, ws.at<int>(T.off_rowpix), m);
     if (st != ST_OK) return st;
   }
@@ -1374,14 +1377,35 @@ extern "C" st_status st_debug_rulebook(st_net* net, int32_t layer,
   if ((st = d2h(net, &nO, cnt + L.cnt_O, 1)) != ST_OK) return st;
   if ((st = d2h(net, &nin, cnt + in.cnt_rows, 1)) != ST_OK) return st;
   std::vector<int> O(nO), rp(nin), nb((size_t)nO * L.K);
-  if ((st = d2h(net, O.data(), ws.at<int>(L.off_O), nO)) != ST_OK) return st;
-  if ((st = d2h(net, rp.data(), ws.at<int>(in.off_rowpix), nin)) != ST_OK)
+  int last_ref = 0;
+  if ((st = d2h(net, &last_ref, ws.at<int>(net->off_se_par) + 1, 1)) != ST_OK)
     return st;
-  for (int k = 0; k < L.K; ++k)
-    if ((st = d2h(net, nb.data() + (size_t)k * nO,
-                  ws.at<int>(L.off_nbr) + (size_t)k * L.conv_grid * net->F, nO)) !=
-        ST_OK)
+  if (last_ref) {
+    // a reference frame's outputs and rows are its pixels, the neighbours
+    // those of the geometry
+    std::iota(O.begin(), O.end(), 0);
+    std::iota(rp.begin(), rp.end(), 0);
+    const st_layer_desc& d = L.d;
+    for (int k = 0; k < L.K; ++k)
+      for (uint64_t o = 0; o < nO; ++o) {
+        const int x = (int)(o % L.Wo), y = (int)(o / L.Wo % L.Ho);
+        const int img = (int)(o / L.Wo / L.Ho);
+        const int iy = y * d.s_h - d.p_h + k / d.k_w;
+        const int ix = x * d.s_w - d.p_w + k % d.k_w;
+        const bool inside = iy >= 0 && iy < L.Hi && ix >= 0 && ix < L.Wi;
+        nb[(size_t)k * nO + o] =
+            inside ? (img * L.Hi + iy) * L.Wi + ix : -1;
+      }
+  } else {
+    if ((st = d2h(net, O.data(), ws.at<int>(L.off_O), nO)) != ST_OK) return st;
+    if ((st = d2h(net, rp.data(), ws.at<int>(in.off_rowpix), nin)) != ST_OK)
       return st;
+    for (int k = 0; k < L.K; ++k)
+      if ((st = d2h(net, nb.data() + (size_t)k * nO,
+                    ws.at<int>(L.off_nbr) + (size_t)k * L.conv_grid * net->F, nO)) !=
+          ST_OK)
+        return st;
+  }
   int64_t cntp = 0;
   for (int k = 0; k < L.K; ++k)
     for (uint64_t o = 0; o < nO; ++o) {

@@ -113,6 +113,9 @@ struct st_net {
   std::vector<st::LayerPlan> layers;
   std::vector<st::TensorPlan> tensors;     // n_layers + 1
   size_t ws_bytes = 0;
+  // of which the reference tables of a net with squeeze-excitation or residual
+  // carry, which do not count against the static workspace's limit
+  size_t static_extra = 0;
   size_t off_xhat = 0;                     // storage dtype [N*H*W*C]
   size_t off_flags = 0;                    // uint8 [input grid] keep bytes
   size_t off_tiles = 0;                    // uint32 [2][kMaxTiles] statuses
@@ -129,7 +132,9 @@ struct st_net {
   bool frozen_se = false;                  // frozen squeeze-excitation gates
   bool bf16_state = false;                 // pre-activation state in bf16
   bool has_se = false;                     // any squeeze-excitation layer
-  size_t off_se_par = 0;                   // int: gate slot of the last gates
+  // int: gate slot of the last gates; int: the last encode was a reference
+  // frame (in device memory, as replayed graphs encode too)
+  size_t off_se_par = 0;
   double ibst_target = 0.9, ibst_eps = 0.025, ibst_theta_max = 1.0;
   // a cycle spans this many reference frames; reference frames seen since
   // the control was set
@@ -147,11 +152,9 @@ struct st_net {
   size_t off_chunk_separt = 0, off_chunk_gates = 0;
   size_t off_cnt = 0;                      // uint64 [n_counters]
   size_t off_cleanup = 0;                  // cleanup descriptor table
-  // dense reference pass (nets without squeeze-excitation or residual
-  // carry): the counters a reference frame leaves (uint64 [n_counters]),
-  // each layer's dense rulebook pair count, and the {offset, length} table
-  // of the kept lists it writes as identities
-  bool dense_ref = false;
+  // dense reference pass: the counters a reference frame leaves (uint64
+  // [n_counters]) and the {offset, length} table of the kept lists it writes
+  // as identities
   size_t off_refcnt = 0, off_iota = 0;
   size_t off_dens = 0;                     // uint64 [batch] per-image counts
   int n_counters = 0;

@@ -34,13 +34,14 @@ void prof_begin(const Prof& p, int cls, hipStream_t s);
 void prof_end(const Prof& p, int cls, hipStream_t s);
 
 // ---- per-frame bookkeeping
-// counters to zero, and the first look-back status set (kCompactMaxTiles)
+// counters and *last_ref to zero, and the first look-back status set
+// (kCompactMaxTiles)
 void launch_reset(const Prof& pf, hipStream_t s, u64* cnt, int n,
-                  uint32_t* status);
+                  uint32_t* status, int* last_ref);
 // dense reference pass: the frame's rows (pixel-ordered, padded to Cp
 // channels) and X_hat = frame; identity kept lists of the tensors (a table
 // of {list offset, length} in the workspace); the frame's counters from a
-// precomputed block
+// precomputed block (and *last_ref = 1)
 void launch_dense_input(const Prof& pf, hipStream_t s, int dtype,
                         const void* x, void* xhat, void* rows, int C, int Cp,
                         int64_t npix);
@@ -49,12 +50,14 @@ struct IotaEntry {  // list[r] = r for r < n
 };
 void launch_iota_lists(const Prof& pf, hipStream_t s, const IotaEntry* tab,
                        int n_tab, char* ws, int64_t max_n);
-void launch_copy_u64(hipStream_t s, u64* dst, const u64* src, int n);
+void launch_ref_counters(hipStream_t s, u64* dst, const u64* src, int n,
+                         int* last_ref);
 // dense max-pool emission of the reference pass: pooled row q (pixel
-// order) = max over the window of f(P) (the state of the conv grid)
+// order) = max over the window of f(P) (the state of the conv grid); ynew:
+// the view that starts as the rows (residual carry) or NULL
 void launch_pool_dense(const Prof& pf, hipStream_t s, int dtype,
-                       const float* P, int p16, void* dout, Geo g, int cp,
-                       int act, int64_t nq);
+                       const float* P, int p16, void* dout, float* ynew,
+                       Geo g, int cp, int act, int64_t nq);
 void launch_cleanup(const Prof& pf, hipStream_t s, const CleanEntry* tab,
                     int n_tab, char* ws, const u64* cnt, int64_t max_rows);
 
@@ -92,7 +95,6 @@ struct ScanArgs {
   int64_t npix;
   float thr;
   const float* thr_dev;  // threshold in device memory (or NULL: thr)
-  int ref;
   uint32_t* tiles;     // look-back statuses of the compaction
   uint32_t* tiles_clear;  // the other status set, cleared for the next one
   void* rows;
@@ -166,7 +168,7 @@ struct ConvArgs {
   uint32_t* rowmax;    // [capO]
   const void* dskip;   // residual delta rows [*, cout_p] or NULL
   const int* mskip;    // residual pixel -> row map
-  int mode, act, ref;
+  int mode, act;
   float keep_thr;      // threshold of the emitted tensor
   const float* keep_thr_dev;  // in device memory (or NULL: keep_thr)
   const void* zero;    // 16 zero bytes (16-byte aligned)
@@ -197,23 +199,37 @@ struct ConvArgs {
   const int* gpar;     // the slot in use (device parity word)
   int64_t gsz;         // floats per slot
   int64_t gate_hw;
-  // dense reference pass: every conv output is a row (row = pixel, nO =
-  // capO), every tensor's rows are pixel-ordered, so the neighbours follow
+  // dense (the reference pass, the REF builds: the state before is zero, the
+  // bias is added): every conv output is a row (row = pixel, nO = capO), every tensor's rows are pixel-ordered, so the neighbours follow
   // from the geometry g (input row of output o at offset k, or -1 in the
   // padding), the residual row of a pixel is the pixel itself, and no row
   // maximum is kept (rowmax NULL)
   int dense;
   Geo g;
   int dense_splits;  // splits of the dense pass's partial rows (0: not split)
+  // residual carry, dense pass: the view [grid][cout_p] that starts as the
+  // emitted rows, or NULL
+  float* ynew;
 };
 // Dense pass: the convolution of every pixel (st_dense.hip).  Returns the
 // number of reduction splits it wrote partial rows for (1: finished).  It
 // takes rows whose 16-byte vectors lie within one pixel (not half-precision
-// rows of 4 channels).
-inline bool dense_conv_rows(int dtype, const ConvArgs& a) {
-  return a.cin_p % (dtype == 0 ? 4 : 8) == 0;
+// rows of 4 channels).  An f32 net with a bf16 state keeps the gather kernel:
+// the dense convolution adds a stage's f32 columns in another order, and each
+// state that a last-bit difference rounds to the other bf16 neighbour moves
+// by 2^-9 (f16 and bf16 columns are added in the same order by both).
+inline bool dense_conv_takes(int dtype, const ConvArgs& a) {
+  return dtype == 0 ? a.cin_p % 4 == 0 && !a.p16 : a.cin_p % 8 == 0;
 }
 int launch_dense_conv(hipStream_t s, int dtype, const ConvArgs& a);
+// Dense pass: a depthwise convolution with a 3x3 or 5x5 window of stride 1 or
+// 2 (dense_dw_takes).
+inline bool dense_dw_takes(const ConvArgs& a) {
+  return a.g.kh == a.g.kw && (a.g.kh == 3 || a.g.kh == 5) &&
+         a.g.sh == a.g.sw && (a.g.sh == 1 || a.g.sh == 2);
+}
+void launch_dense_dw(const Prof& pf, hipStream_t s, int dtype,
+                     const ConvArgs& a, int images);
 // Returns false (and launches nothing) when a.zero is missing or misaligned.
 bool launch_conv_gemm(const Prof& pf, hipStream_t s, int dtype,
                       const ConvArgs& a);
@@ -231,13 +247,13 @@ struct PoolArgs {
   const int* Mo;       // conv pixel -> O index or -1
   void* dout;
   uint32_t* rowmax;
-  int cp, act, ref;
+  int cp, act;
   const float* yhat;    // residual carry view (pooled grid) or NULL
 };
 void launch_pool_emit(const Prof& pf, hipStream_t s, int dtype,
                       const PoolArgs& a);
 void launch_commit(const Prof& pf, hipStream_t s, const int* O, const u64* nO,
-                   int64_t capO, float* P, const float* dP, int cp, int ref);
+                   int64_t capO, float* P, const float* dP, int cp);
 
 // ---- truncation of an emitted tensor (list-mode compaction)
 struct ListArgs {
@@ -261,7 +277,7 @@ struct SeArgs {
   int p16;             // state stored as bf16
   const float* P;      // state [npix][cp] (updated in place by the emission)
   const float* dP;     // deferred update rows
-  const int* Mo;       // site -> dP row or -1 (every site in the reference)
+  const int* Mo;       // site -> dP row or -1
   float* part;         // [N][nchunk][cp] partial sums of this frame's change
   double* S;           // [N][cp] channel sums of f(P), kept across frames
   const float* w1;     // [mid][cp]
@@ -282,6 +298,9 @@ struct SeArgs {
   float keep_thr;
   const float* keep_thr_dev;  // in device memory (or NULL: keep_thr)
   const float* yhat;          // residual carry view or NULL
+  // reference pass (ref: every site's state is in P, S starts at zero): the
+  // view that starts as the rows, or NULL
+  float* ynew;
   float* gout;                // excitation: gates to [N][cp] here (the last
                               // frame's to the new slot too) instead of the
                               // new slot (or NULL)

@@ -447,7 +447,7 @@ struct ScanPred {
   int* rowpix;
   int* act;
   int* map;
-  int C, Cp, ref;
+  int C, Cp;
   float thr;
   const float* thr_dev;
   ConsList cons;
@@ -459,7 +459,7 @@ struct ScanPred {
     const float thr = thr_dev ? *thr_dev : this->thr;
     float m = 0.f;
     for (int c = 0; c < C; ++c) {
-      float d = to_f(x[i * C + c]) - (ref ? 0.f : to_f(xhat[i * C + c]));
+      float d = to_f(x[i * C + c]) - to_f(xhat[i * C + c]);
       m = fmaxf(m, fabsf(d));
     }
     return Item{(uint8_t)(m > thr ? 1 : 0)};
@@ -474,7 +474,7 @@ struct ScanPred {
     for (int c = 0; c < Cp; ++c) {
       if (c < C) {
         const T xv = x[i * C + c];
-        const float d = to_f(xv) - (ref ? 0.f : to_f(xhat[i * C + c]));
+        const float d = to_f(xv) - to_f(xhat[i * C + c]);
         r[c] = from_f<T>(d);
         xhat[i * C + c] = xv;
       } else {
@@ -492,7 +492,7 @@ struct ScanPred {
 template <typename T>
 static void scan_t(const Prof& pf, hipStream_t s, const ScanArgs& a) {
   ScanPred<T> p{(const T*)a.x, (T*)a.xhat, (T*)a.rows, a.rowpix, a.act,
-                a.map, a.C, a.Cp, a.ref, a.thr, a.thr_dev, a.cons};
+                a.map, a.C, a.Cp, a.thr, a.thr_dev, a.cons};
   run_compact(pf, 1 /*ST_K_SCAN_COMPACT*/, s, nullptr, a.npix, a.npix,
               a.tiles, a.tiles_clear, a.cnt_rows, a.cnt_act, p);
 }
@@ -830,6 +830,7 @@ __device__ __forceinline__ float finish_cols(const ConvArgs& a, LoadV load_v,
       if (a.mode == kModeStateOnly) continue;
     }
     rm = fmaxf(rm, Vec8<T>::store(dout + eo * cout_p + n, v));
+    if (REF && a.ynew) store8f_rounded<T>(a.ynew + eo * cout_p + n, v);
   }
   return rm;
 }
@@ -1163,7 +1164,7 @@ void k_conv_gemm(ConvArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int l16 = lane & 15, lg = lane >> 4;
-  const int64_t nO = a.dense ? a.capO : (int64_t)*a.nO;
+  const int64_t nO = REF ? a.capO : (int64_t)*a.nO;
   // row tiles: 64 rows each, or (chunk-state mode) aligned to site runs
   const bool runs = CHUNK;  // the launcher pairs tstart with this mode
   const int rstep = runs ? chunk_tile_step(a.nf) : BM;
@@ -1193,7 +1194,7 @@ void k_conv_gemm(ConvArgs a) {
   // epilogue ownership: thread -> row em, columns [ec, ec + 16) of a
   // 64-column quarter
   const int em = tid >> 2, ec = (tid & 3) * 16;
-  if (REF && a.dense && tid < K) {
+  if (REF && tid < K) {
     const int ky = tid / a.g.kw;
     s_koff[tid] = (ky << 16) | (tid - ky * a.g.kw);
   }
@@ -1230,8 +1231,8 @@ void k_conv_gemm(ConvArgs a) {
     // now so that they arrive while the reduction runs
     const int64_t eo = m0 + em;
     const bool eok = eo < m1;
-    const int epix = !eok ? 0 : a.dense ? (int)eo : a.O[eo];
-    if (REF && a.dense && tid < BM) {
+    const int epix = !eok ? 0 : REF ? (int)eo : a.O[eo];
+    if (REF && tid < BM) {
       const int64_t o = m0 + tid;
       const unsigned op = o < m1 ? (unsigned)o : 0u;
       const unsigned hwo = (unsigned)a.g.Ho * (unsigned)a.g.Wo;
@@ -1249,7 +1250,7 @@ void k_conv_gemm(ConvArgs a) {
       const int64_t o = m0 + m;
       int src = -1;
       if (o < m1) {
-        if (REF && a.dense) {
+        if (REF) {
           const int ko = s_koff[k];
           const int iy = s_dorg[BM + m] + (ko >> 16);
           const int ix = s_dorg[2 * BM + m] + (ko & 0xffff);
@@ -1463,7 +1464,7 @@ void k_conv_gemm(ConvArgs a) {
     // this thread's output row's residual row, requested now so that it
     // arrives during the reduction; (chunk-state mode) the row's site
     const int rsk = (!SPLIT && a.mskip && eok)
-                        ? (a.dense ? epix : a.mskip[epix])
+                        ? (REF ? epix : a.mskip[epix])
                         : -1;
     if (CHUNK && (tid & 3) == 0) {
       s_site[em] = eok ? (int)((unsigned)epix % (unsigned)a.per) : -1;
@@ -1600,11 +1601,11 @@ void k_conv_gemm(ConvArgs a) {
 template <typename T, bool REF>
 __global__ __launch_bounds__(256) void k_split_epi(ConvArgs a) {
   constexpr int BM = kGemmBM, BN = kGemmBN;
-  const int64_t nO = a.dense ? a.capO : (int64_t)*a.nO;
+  const int64_t nO = REF ? a.capO : (int64_t)*a.nO;
   const int64_t tiles_m = (nO + BM - 1) / BM;
   const int tiles_n = (a.cout_p + BN - 1) / BN;
   const int64_t ntiles = tiles_m * tiles_n;
-  const int S = a.dense
+  const int S = REF && a.dense_splits
                     ? a.dense_splits
                     : split_count(ntiles, gemm_stages<T>(a), a.split_max);
   const int tid = threadIdx.x, cout_p = a.cout_p;
@@ -1616,7 +1617,7 @@ __global__ __launch_bounds__(256) void k_split_epi(ConvArgs a) {
     const int n0 = (int)(t - tm_i * tiles_n) * BN;
     const int64_t eo = m0 + em;
     const bool eok = eo < nO;
-    const int epix = !eok ? 0 : a.dense ? (int)eo : a.O[eo];
+    const int epix = !eok ? 0 : REF ? (int)eo : a.O[eo];
     bool hv[2];
     float po[2][8], sk[2][8];
 #pragma unroll
@@ -1629,7 +1630,7 @@ __global__ __launch_bounds__(256) void k_split_epi(ConvArgs a) {
         state_load8(a.P, a.p16, (int64_t)epix * cout_p + n, po[h]);
     }
     const int rsk =
-        (a.mskip && eok) ? (a.dense ? epix : a.mskip[epix]) : -1;
+        (a.mskip && eok) ? (REF ? epix : a.mskip[epix]) : -1;
 #pragma unroll
     for (int h = 0; h < 2; ++h)
       if (hv[h] && rsk >= 0)
@@ -1990,7 +1991,7 @@ static void gemm_big_t(hipStream_t s, int grid, size_t lds,
 
 template <typename T>
 static void split_epi_t(hipStream_t s, int grid, const ConvArgs& a) {
-  if (a.ref)
+  if (a.dense)
     k_split_epi<T, true><<<grid, 256, 0, s>>>(a);
   else
     k_split_epi<T, false><<<grid, 256, 0, s>>>(a);
@@ -2178,7 +2179,7 @@ void k_stem_dense(ConvArgs a) {
 // The dense reference pass's stem takes k_stem_dense: half precision, 7x7
 // stride 2 over rows of 4 (padded) channels, at most 64 output channels.
 static bool stem_dense(int dtype, const ConvArgs& a) {
-  return dtype != 0 && a.ref && a.dense && a.K == 49 && a.cin_p == 4 &&
+  return dtype != 0 && a.dense && a.K == 49 && a.cin_p == 4 &&
          a.cout_p <= 64 && a.g.kh == 7 && a.g.kw == 7 && a.g.sh == 2 &&
          a.g.sw == 2 && a.split_max <= 1 && a.g.Wo > 0;
 }
@@ -2189,9 +2190,10 @@ using GemmFn = void (*)(ConvArgs);
 template <typename T, bool SPLIT>
 static GemmFn pick_gemm(const ConvArgs& a) {
   const bool aligned = a.cin_p % GemmTile<T>::KC == 0;
-  if (a.ref)
-    return aligned ? k_conv_gemm<T, true, true, SPLIT, false>
-                   : k_conv_gemm<T, true, false, SPLIT, false>;
+  if constexpr (sizeof(T) == 4)
+    if (a.dense)
+      return aligned ? k_conv_gemm<T, true, true, SPLIT, false>
+                     : k_conv_gemm<T, true, false, SPLIT, false>;
   if (!SPLIT && a.mode == kModeChunkState)  // builds of their own
     return aligned ? k_conv_gemm<T, false, true, false, true>
                    : k_conv_gemm<T, false, false, false, true>;
@@ -2248,7 +2250,7 @@ static int persistent_grid(int64_t units, const void* fn, size_t lds,
 // input channels, or a 1x1 layer with 1024, is 2% to 25% slower with them
 // (half the resident waves, and row tiles of half the count).
 static bool use_big(int dtype, const ConvArgs& a) {
-  return dtype != 0 && a.mode == kModeChunkState && !a.ref &&
+  return dtype != 0 && a.mode == kModeChunkState &&
          a.split_max <= 1 && a.cout_p % kBigBN == 0 && a.cin_p % 64 == 0 &&
          a.K <= 64 && ((a.K > 1 && a.cin_p >= 256) || a.cin_p >= 2048);
 }
@@ -2276,7 +2278,7 @@ bool launch_conv_gemm(const Prof& pf, hipStream_t s, int dtype,
     prof_end(pf, 7, s);
     return true;
   }
-  if (a.dense && dense_conv_rows(dtype, a)) {
+  if (a.dense && dense_conv_takes(dtype, a)) {
     prof_begin(pf, 7 /*ST_K_CONV_GEMM*/, s);
     const int splits = launch_dense_conv(s, dtype, a);
     prof_end(pf, 7, s);
@@ -2301,9 +2303,15 @@ bool launch_conv_gemm(const Prof& pf, hipStream_t s, int dtype,
       ((a.capO + rstep - 1) / rstep) * ((a.cout_p + kGemmBN - 1) / kGemmBN);
   const int64_t units = worst * (a.split_max > 1 ? a.split_max : 1);
   const size_t lds = sizeof(int) * (size_t)a.K * kGemmBM;
-  const GemmFn fn = dtype == 0   ? pick_gemm<float>(a)
-                    : dtype == 1 ? pick_gemm<_Float16>(a)
-                                 : pick_gemm<bf16_t>(a);
+  // dense: what the dense convolution does not take (half-precision rows of
+  // 4 channels are never split: a.K * 4 columns)
+  const GemmFn fn =
+      a.dense && dtype != 0
+          ? (dtype == 1 ? k_conv_gemm<_Float16, true, false, false, false>
+                        : k_conv_gemm<bf16_t, true, false, false, false>)
+      : dtype == 0 ? pick_gemm<float>(a)
+      : dtype == 1 ? pick_gemm<_Float16>(a)
+                   : pick_gemm<bf16_t>(a);
   // persistent blocks: what the CUs hold at once (a large window's
   // neighbour table can leave room for fewer than four)
   const int grid = persistent_grid(units, (const void*)fn, lds,
@@ -2330,14 +2338,14 @@ __device__ __forceinline__ void conv_dw_rows(const ConvArgs& a) {
   const T* dskip = (const T*)a.dskip;
   T* dout = (T*)a.dout;
   const int cout_p = a.cout_p, cin_p = a.cin_p;
-  const int64_t nO = a.dense ? a.capO : (int64_t)*a.nO;
+  const int64_t nO = REF ? a.capO : (int64_t)*a.nO;
   const int cpr = cout_p / 8;
   const int64_t total = nO * cpr;
   for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total;
        idx += (int64_t)gridDim.x * 256) {
     const int64_t o = idx / cpr;
     const int c0 = (int)(idx - o * cpr) * 8;
-    const int pix = a.dense ? (int)o : a.O[o];
+    const int pix = REF ? (int)o : a.O[o];
     float acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.f;
@@ -2346,7 +2354,7 @@ __device__ __forceinline__ void conv_dw_rows(const ConvArgs& a) {
 #pragma unroll
       for (int j = 0; j < KB; ++j)
         src[j] = k0 + j >= a.K ? -1
-                 : a.dense     ? dense_src(a.g, o, k0 + j)
+                 : REF         ? dense_src(a.g, o, k0 + j)
                                : a.nbr[(int64_t)(k0 + j) * a.stride + o];
       uint4 raw[KB][RV];
 #pragma unroll
@@ -2368,7 +2376,7 @@ __device__ __forceinline__ void conv_dw_rows(const ConvArgs& a) {
       }
     }
     // every load of the epilogue before its stores
-    const int rsk = !a.mskip ? -1 : a.dense ? pix : a.mskip[pix];
+    const int rsk = !a.mskip ? -1 : REF ? pix : a.mskip[pix];
     float sk[8], po[8], ex[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) sk[e] = po[e] = 0.f;
@@ -2412,6 +2420,7 @@ __device__ __forceinline__ void conv_dw_rows(const ConvArgs& a) {
       }
     }
     const float rm = Vec8<T>::store(dout + o * cout_p + c0, v);
+    if (REF && a.ynew) store8f_rounded<T>(a.ynew + o * cout_p + c0, v);
     if (rm > 0.f && a.rowmax) atomicMax(a.rowmax + o, __float_as_uint(rm));
   }
 }
@@ -2425,7 +2434,7 @@ __global__ __launch_bounds__(256) void k_conv_dw(ConvArgs a) {
 
 template <typename T>
 static void dw_t(hipStream_t s, int grid, const ConvArgs& a) {
-  if (a.ref)
+  if (a.dense)
     k_conv_dw<T, true><<<grid, 256, 0, s>>>(a);
   else
     k_conv_dw<T, false><<<grid, 256, 0, s>>>(a);
@@ -2470,7 +2479,7 @@ __global__ __launch_bounds__(256) void k_pool_emit(PoolArgs a) {
         const int ix = qx * g.sw - g.pw + kx;
         if (ix < 0 || ix >= g.Wi) continue;
         const int64_t w = ((int64_t)n * g.Hi + iy) * g.Wi + ix;
-        const float po = a.ref ? 0.f : a.P[w * a.cp + c];
+        const float po = a.P[w * a.cp + c];
         const int r = a.Mo[w];
         const float pn = r >= 0 ? po + a.dP[(int64_t)r * a.cp + c] : po;
         mo = fmaxf(mo, act_f(po, a.act));
@@ -2478,7 +2487,7 @@ __global__ __launch_bounds__(256) void k_pool_emit(PoolArgs a) {
       }
     }
     // residual carry: against what the consumers received
-    if (a.yhat && !a.ref) mo = a.yhat[(int64_t)p * a.cp + c];
+    if (a.yhat) mo = a.yhat[(int64_t)p * a.cp + c];
     const T qv = from_f<T>(mn - mo);
     dout[q * a.cp + c] = qv;
     const float ab = fabsf(to_f(qv));
@@ -2501,7 +2510,7 @@ void launch_pool_emit(const Prof& pf, hipStream_t s, int dtype,
 
 __global__ __launch_bounds__(256) void k_commit(const int* O, const u64* nOp,
                                                 float* P, const float* dP,
-                                                int cp, int ref) {
+                                                int cp) {
   const int64_t nO = (int64_t)*nOp;
   const int c4 = cp / 4;
   const int64_t total = nO * c4;
@@ -2511,17 +2520,17 @@ __global__ __launch_bounds__(256) void k_commit(const int* O, const u64* nOp,
     const int c = (int)(idx - o * c4) * 4;
     float4* pp = (float4*)(P + (int64_t)O[o] * cp + c);
     const float4 d = *(const float4*)(dP + o * cp + c);
-    float4 v = ref ? make_float4(0.f, 0.f, 0.f, 0.f) : *pp;
+    float4 v = *pp;
     v.x += d.x; v.y += d.y; v.z += d.z; v.w += d.w;
     *pp = v;
   }
 }
 
 void launch_commit(const Prof& pf, hipStream_t s, const int* O, const u64* nO,
-                   int64_t capO, float* P, const float* dP, int cp, int ref) {
+                   int64_t capO, float* P, const float* dP, int cp) {
   prof_begin(pf, 13 /*ST_K_COMMIT*/, s);
-  k_commit<<<grid_for(capO * (cp / 4), 8192), 256, 0, s>>>(O, nO, P, dP, cp,
-                                                           ref);
+  k_commit<<<grid_for(capO * (cp / 4), 8192), 256, 0, s>>>(O, nO, P, dP,
+                                                           cp);
   prof_end(pf, 13, s);
 }
 
@@ -2589,8 +2598,8 @@ __host__ __device__ __forceinline__ int round_up8(int x) {
 // Exact squeeze-excitation on a deferred layer (state P, update rows dP of
 // the affected sites, Mo: site -> dP row).  The pooled mean of f(P) is kept
 // as per-image f64 channel sums S that each frame moves by
-// sum over affected sites of f(P_new) - f(P_old) (in the reference pass:
-// by f(P) over every site, from S = 0).  Squeeze: partial sums of that
+// sum over affected sites of f(P_new) - f(P_old) (in the reference pass,
+// whose states are in P already: by f(P) over every site, from S = 0).  Squeeze: partial sums of that
 // change over fixed site ranges; excite: S, mean and gates per image;
 // emit: delta = f(P_new) * s_new - f(P_old) * s_old at every site, the state
 // commit, row maxima and the 64-site kept counts.  Every sum runs in a fixed
@@ -2623,12 +2632,7 @@ __global__ __launch_bounds__(256) void k_se_squeeze(SeArgs a) {
       const int v = lane + k * TPS;
       if (v >= V) break;
       float po[8], dp[8];
-      if (a.ref) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) po[e] = 0.f;
-      } else {
-        state_load8(a.P, a.p16, p * cp + v * 8, po);
-      }
+      state_load8(a.P, a.p16, p * cp + v * 8, po);
       load8f(a.dP + (int64_t)r * cp + v * 8, dp);
 #pragma unroll
       for (int e = 0; e < 8; ++e)
@@ -2665,56 +2669,59 @@ __global__ __launch_bounds__(256) void k_se_squeeze(SeArgs a) {
 // of all frames come first (k_se_means, 64 channels of one image per block),
 // then every frame's and image's gates at once (k_se_gates).
 //
-// Means: 16 lanes per 4-channel column sum a frame's partials over the site
-// chunks, the lanes' sums are added in lane order and move the f64 sums S
-// frame by frame.  Frame t's means go to the first chunk's row of its
-// partials, which only this block reads.
-constexpr int kSeMeanFrames = 8;  // frames whose partials are held at once
-__global__ __launch_bounds__(256) void k_se_means(SeArgs a) {
-  __shared__ float4 red[kSeMeanFrames][256];
-  __shared__ float tot[kSeMeanFrames][64];
+// Means: a column of 4 channels has `lanes` threads, each summing every
+// lanes-th site chunk's partials of a frame; the lanes' sums are added in lane
+// order and move the f64 sums S frame by frame.  A block takes `cols` columns
+// and up to `fb` frames at once.  Frame t's means go to the first chunk's row
+// of its partials, which only this block reads.
+constexpr int kSeMeanVecs = 2048;  // lane sums a block holds
+constexpr int kSeMeanTots = 512;   // and channel sums
+__global__ void k_se_means(SeArgs a, int lanes, int cols, int fb) {
+  __shared__ float4 red[kSeMeanVecs];
+  __shared__ float tot[kSeMeanTots];
   const int n = blockIdx.y, cp = a.cp, V4 = cp / 4, tid = threadIdx.x;
-  const int v = blockIdx.x * 16 + (tid & 15), l = tid >> 4;
+  const int NT = blockDim.x, W = 4 * cols;
+  const int v = blockIdx.x * cols + tid % cols, l = tid / cols;
   const int nfr = a.nfr > 1 ? a.nfr : 1;
-  const int c = blockIdx.x * 64 + (tid & 63);
+  const int c = blockIdx.x * W + tid;
+  const bool owner = tid < W && c < cp;
   double* S = a.S + (int64_t)n * cp + c;
   double sum = 0.0;
-  if (tid < 64 && c < cp && !a.ref) sum = *S;
-  for (int f0 = 0; f0 < nfr; f0 += kSeMeanFrames) {
-    const int nb = min(kSeMeanFrames, nfr - f0);
+  if (owner && !a.ref) sum = *S;
+  for (int f0 = 0; f0 < nfr; f0 += fb) {
+    const int nb = min(fb, nfr - f0);
     for (int f = 0; f < nb; ++f) {
       const float4* part = (const float4*)(a.part +
                                            (f0 + f) * a.part_stride +
                                            (int64_t)n * a.nchunk * cp);
       float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (v < V4) {
+      if (v < V4 && l < lanes) {
 #pragma unroll 8
-        for (int g = l; g < a.nchunk; g += 16) {
+        for (int g = l; g < a.nchunk; g += lanes) {
           const float4 q = part[(int64_t)g * V4 + v];
           acc.x += q.x; acc.y += q.y; acc.z += q.z; acc.w += q.w;
         }
       }
-      red[f][tid] = acc;
+      red[f * NT + tid] = acc;
     }
     __syncthreads();
-    for (int i = tid; i < nb * 64; i += 256) {
-      const int f = i >> 6, k = i & 63;
-      const float* r = (const float*)red[f] + k;
+    for (int i = tid; i < nb * W; i += NT) {
+      const int f = i / W, k = i - f * W;
+      const float* r = (const float*)(red + f * NT) + k;
       float s = r[0];
-#pragma unroll
-      for (int j = 1; j < 16; ++j) s += r[64 * j];
-      tot[f][k] = s;
+      for (int j = 1; j < lanes; ++j) s += r[W * j];
+      tot[i] = s;
     }
     __syncthreads();
-    if (tid < 64 && c < cp)
+    if (owner)
       for (int f = 0; f < nb; ++f) {
-        sum += (double)tot[f][tid];
+        sum += (double)tot[f * W + tid];
         a.part[(f0 + f) * a.part_stride + (int64_t)n * a.nchunk * cp + c] =
             (float)(sum / (double)a.hw);
       }
     // (the next turn writes red before its first barrier and tot after it)
   }
-  if (tid < 64 && c < cp) *S = sum;
+  if (owner) *S = sum;
 }
 
 // Gates of image blockIdx.x in frame blockIdx.y from its means: the hidden
@@ -2831,7 +2838,14 @@ __global__ __launch_bounds__(kSeExciteThreads) void k_se_gates(SeArgs a) {
 
 static void se_excite(const Prof& pf, hipStream_t s, const SeArgs& a) {
   prof_begin(pf, 20 /*ST_K_SE_EXCITE*/, s);
-  k_se_means<<<dim3((a.cp + 63) / 64, a.N), 256, 0, s>>>(a);
+  // lanes per column from the channels alone; up to 16 columns a block (64
+  // channels of an image), and as many frames as the block's lane sums allow
+  const int V4 = a.cp / 4, lanes = kSeExciteThreads / V4;
+  const int cols = lanes >= 256 ? 1 : 256 / lanes > 16 ? 16 : 256 / lanes;
+  const int nt = (cols * lanes + 63) / 64 * 64;
+  const int by_red = kSeMeanVecs / nt, by_tot = kSeMeanTots / (4 * cols);
+  k_se_means<<<dim3((V4 + cols - 1) / cols, a.N), nt, 0, s>>>(
+      a, lanes, cols, by_red < by_tot ? by_red : by_tot);
   k_se_gates<<<dim3(a.N, a.nfr > 1 ? a.nfr : 1), kSeExciteThreads,
                sizeof(float) * (a.cp + round_up8(a.mid) +
                                 4 * kSeExciteThreads),
@@ -2859,12 +2873,7 @@ __global__ __launch_bounds__(256) void k_se_emit(SeArgs a) {
       if (v >= V) break;
       const int c0 = v * 8;
       float po[8], dp[8], gn[8], go[8], pn[8], d[8];
-      if (a.ref) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) po[e] = 0.f;
-      } else {
-        state_load8(a.P, a.p16, row * cp + c0, po);
-      }
+      state_load8(a.P, a.p16, row * cp + c0, po);
       if (r >= 0) {
         load8f(a.dP + (int64_t)r * cp + c0, dp);
       } else {
@@ -2872,16 +2881,14 @@ __global__ __launch_bounds__(256) void k_se_emit(SeArgs a) {
         for (int e = 0; e < 8; ++e) dp[e] = 0.f;
       }
       load8f(sn + c0, gn);
-      const bool carry = a.yhat && !a.ref;
+      const bool carry = a.yhat != nullptr;
       // residual carry: against what the consumers received
       load8f(carry ? a.yhat + row * cp + c0 : so + c0, go);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         pn[e] = state_round(a.p16, po[e] + dp[e]);
         const float en = act_f(pn[e], a.act) * gn[e];
-        const float eo = a.ref     ? 0.f
-                         : carry   ? go[e]
-                                   : act_f(po[e], a.act) * go[e];
+        const float eo = carry ? go[e] : act_f(po[e], a.act) * go[e];
         d[e] = en - eo;
       }
       rm = fmaxf(rm, Vec8<T>::store(dout + row * cp + c0, d));
@@ -2898,12 +2905,118 @@ __global__ __launch_bounds__(256) void k_se_emit(SeArgs a) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *a.cnt_rows = (u64)a.npix;
 }
 
+// Squeeze of the reference pass, whose states are all in P: the sums of f(P)
+// over the squeeze's site chunks, lanes and tree (the means of a reference
+// frame then come out as those of a diff frame that changed everything), but
+// `lanes` channel vectors per block: with all of a site's channels in one
+// block a deep layer of one image had 14 blocks, bound by their own SiLUs
+// (EfficientNet-B0 at 512x512: 250 us for 16 layers, now 120 us).
+__global__ __launch_bounds__(256) void k_dense_se_squeeze(SeArgs a, int lanes,
+                                                          int R) {
+  __shared__ float sm[256 * 8];  // [R][lanes * 8]
+  const int n = blockIdx.y, g = blockIdx.x, cp = a.cp, W = lanes * 8;
+  const int lane = threadIdx.x % lanes, rl = threadIdx.x / lanes;
+  const int cb = (int)blockIdx.z * W, c0 = cb + lane * 8;
+  const int64_t base = (int64_t)n * a.hw;
+  const int64_t s0 = (int64_t)g * a.chunk;
+  const int64_t s1 = min(s0 + (int64_t)a.chunk, a.hw);
+  float acc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  with_act(a.act, [&](auto act_tag) {
+    // four sites' states are requested at a time
+    for (int64_t si = s0 + rl; c0 < cp && si < s1; si += 4 * R) {
+      float po[4][8];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        state_load8(a.P, a.p16, (base + min(si + j * R, s1 - 1)) * cp + c0,
+                    po[j]);
+#pragma unroll 1
+      for (int j = 0; j < 4 && si + j * R < s1; ++j) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          acc[e] += act_c<decltype(act_tag)::value>(po[0][e]);
+#pragma unroll
+        for (int q = 1; q < 4; ++q)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) po[q - 1][e] = po[q][e];
+      }
+    }
+  });
+  store8f(sm + rl * W + lane * 8, acc);
+  __syncthreads();
+  for (int h = R / 2; h > 0; h >>= 1) {
+    for (int i = threadIdx.x; i < h * W; i += blockDim.x) sm[i] += sm[h * W + i];
+    __syncthreads();
+  }
+  for (int i = threadIdx.x; i < W && cb + i < cp; i += blockDim.x)
+    a.part[((int64_t)n * a.nchunk + g) * cp + cb + i] = sm[i];
+}
+
+// Emission of the reference pass: every site's row is f(P) * s (the state
+// before is zero), which residual carry's view starts as.  A streaming pass:
+// one thread holds its 8 channels' gates and takes four sites, `to` threads
+// side by side on a site's channels.
+template <typename T>
+__global__ __launch_bounds__(256) void k_dense_se_emit(SeArgs a, int to) {
+  const int R = 256 / to, oct = threadIdx.x % to, rl = threadIdx.x / to;
+  const int cp = a.cp, n = blockIdx.y;
+  const int c0 = ((int)blockIdx.z * to + oct) * 8;
+  if (rl >= R || c0 >= cp) return;
+  float g[8];
+  load8f(gate_slot(a.gates, a.gpar, a.gsz, 1) + (int64_t)n * cp + c0, g);
+  const int64_t s0 = (int64_t)blockIdx.x * R * 4 + rl;
+  float v[4][8];
+  // f(P) * s minus the zero state's emission, fused as the diff frames' is
+  // (f16 rows then round once), so the zero must not be known to the compiler
+  float zero = -0.f;
+  asm("" : "+v"(zero));
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    if (s0 + j * R < a.hw)
+      state_load8(a.P, a.p16, ((int64_t)n * a.hw + s0 + j * R) * cp + c0,
+                  v[j]);
+  with_act(a.act, [&](auto act_tag) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (s0 + j * R >= a.hw) break;
+      const int64_t at = ((int64_t)n * a.hw + s0 + j * R) * cp + c0;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        v[j][e] = __builtin_fmaf(act_c<decltype(act_tag)::value>(v[j][e]),
+                                 g[e], zero);
+      (void)Vec8<T>::store((T*)a.dout + at, v[j]);
+      if (a.ynew) store8f_rounded<T>(a.ynew + at, v[j]);
+    }
+  });
+}
+
 template <int TPS>
 static void se_t(const Prof& pf, hipStream_t s, int dtype, const SeArgs& a) {
   prof_begin(pf, 19 /*ST_K_SE_SQUEEZE*/, s);
-  k_se_squeeze<TPS><<<dim3(a.nchunk, a.N), 256, 0, s>>>(a);
+  if (a.ref) {
+    const int lanes = TPS < 16 ? TPS : 16, rows = 256 / TPS;
+    k_dense_se_squeeze<<<dim3(a.nchunk, a.N, (a.cp / 8 + lanes - 1) / lanes),
+                         lanes * rows, 0, s>>>(a, lanes, rows);
+  } else {
+    k_se_squeeze<TPS><<<dim3(a.nchunk, a.N), 256, 0, s>>>(a);
+  }
   prof_end(pf, 19, s);
   se_excite(pf, s, a);
+  if (a.ref) {
+    const int to = octets_per_block(a.cp / 8), R4 = 256 / to * 4;
+    const dim3 grid((unsigned)((a.hw + R4 - 1) / R4), a.N,
+                    (a.cp / 8 + to - 1) / to);
+    prof_begin(pf, 21 /*ST_K_SE_EMIT*/, s);
+    if (dtype == 0)
+      k_dense_se_emit<float><<<grid, 256, 0, s>>>(a, to);
+    else if (dtype == 1)
+      k_dense_se_emit<_Float16><<<grid, 256, 0, s>>>(a, to);
+    else
+      k_dense_se_emit<bf16_t><<<grid, 256, 0, s>>>(a, to);
+    prof_end(pf, 21, s);
+    return;
+  }
   constexpr int R = 256 / TPS;
   const int blocks = (int)((a.npix + R - 1) / R);
   prof_begin(pf, 21 /*ST_K_SE_EMIT*/, s);
@@ -3793,16 +3906,17 @@ void launch_flip_parity(hipStream_t s, int* par) {
 }
 
 // ------------------------------------------------------- bookkeeping
-__global__ void k_reset(u64* cnt, int n, uint32_t* status) {
+__global__ void k_reset(u64* cnt, int n, uint32_t* status, int* last_ref) {
+  if (threadIdx.x == 0) *last_ref = 0;
   for (int i = threadIdx.x; i < n; i += blockDim.x) cnt[i] = 0ull;
   for (int i = threadIdx.x; i < kCompactMaxTiles; i += blockDim.x)
     status[i] = 0u;
 }
 
 void launch_reset(const Prof& pf, hipStream_t s, u64* cnt, int n,
-                  uint32_t* status) {
+                  uint32_t* status, int* last_ref) {
   prof_begin(pf, 18 /*ST_K_RESET*/, s);
-  k_reset<<<1, 256, 0, s>>>(cnt, n, status);
+  k_reset<<<1, 256, 0, s>>>(cnt, n, status, last_ref);
   prof_end(pf, 18, s);
 }
 
@@ -3881,12 +3995,15 @@ void launch_iota_lists(const Prof& pf, hipStream_t s, const IotaEntry* tab,
   prof_end(pf, 17, s);
 }
 
-__global__ void k_copy_u64(u64* dst, const u64* src, int n) {
+__global__ void k_ref_counters(u64* dst, const u64* src, int n,
+                               int* last_ref) {
+  if (threadIdx.x == 0) *last_ref = 1;
   for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
 }
 
-void launch_copy_u64(hipStream_t s, u64* dst, const u64* src, int n) {
-  k_copy_u64<<<1, 256, 0, s>>>(dst, src, n);
+void launch_ref_counters(hipStream_t s, u64* dst, const u64* src, int n,
+                         int* last_ref) {
+  k_ref_counters<<<1, 256, 0, s>>>(dst, src, n, last_ref);
 }
 
 // One thread per 8 channels of a pooled pixel: the largest f(P) over the
@@ -3895,8 +4012,9 @@ void launch_copy_u64(hipStream_t s, u64* dst, const u64* src, int n) {
 // state (max f(P) - max f(0), f(0) = 0).
 template <typename T, int ACT>
 __device__ __forceinline__ void pool_dense_rows(const float* P, int p16,
-                                                T* dout, const Geo& g,
-                                                int cp, int64_t nq) {
+                                                T* dout, float* ynew,
+                                                const Geo& g, int cp,
+                                                int64_t nq) {
   const int cpr = cp / 8;
   const int64_t hwq = (int64_t)g.Ho * g.Wo;
   for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -3923,32 +4041,35 @@ __device__ __forceinline__ void pool_dense_rows(const float* P, int p16,
       }
     }
     (void)Vec8<T>::store(dout + q * cp + c0, m);
+    if (ynew) store8f_rounded<T>(ynew + q * cp + c0, m);
   }
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_pool_dense(const float* P, int p16,
-                                                    T* dout, Geo g, int cp,
-                                                    int act, int64_t nq) {
+                                                    T* dout, float* ynew,
+                                                    Geo g, int cp, int act,
+                                                    int64_t nq) {
   with_act(act, [&](auto act_tag) {
-    pool_dense_rows<T, decltype(act_tag)::value>(P, p16, dout, g, cp, nq);
+    pool_dense_rows<T, decltype(act_tag)::value>(P, p16, dout, ynew, g, cp,
+                                                 nq);
   });
 }
 
 void launch_pool_dense(const Prof& pf, hipStream_t s, int dtype,
-                       const float* P, int p16, void* dout, Geo g, int cp,
-                       int act, int64_t nq) {
+                       const float* P, int p16, void* dout, float* ynew,
+                       Geo g, int cp, int act, int64_t nq) {
   const int grid = grid_for(nq * (cp / 8), 8192);
   prof_begin(pf, 12 /*ST_K_POOL_EMIT*/, s);
   if (dtype == 0)
-    k_pool_dense<float><<<grid, 256, 0, s>>>(P, p16, (float*)dout, g, cp,
-                                             act, nq);
+    k_pool_dense<float><<<grid, 256, 0, s>>>(P, p16, (float*)dout, ynew, g,
+                                             cp, act, nq);
   else if (dtype == 1)
-    k_pool_dense<_Float16><<<grid, 256, 0, s>>>(P, p16, (_Float16*)dout, g,
-                                                cp, act, nq);
+    k_pool_dense<_Float16><<<grid, 256, 0, s>>>(P, p16, (_Float16*)dout, ynew,
+                                                g, cp, act, nq);
   else
-    k_pool_dense<bf16_t><<<grid, 256, 0, s>>>(P, p16, (bf16_t*)dout, g, cp,
-                                              act, nq);
+    k_pool_dense<bf16_t><<<grid, 256, 0, s>>>(P, p16, (bf16_t*)dout, ynew, g,
+                                              cp, act, nq);
   prof_end(pf, 12, s);
 }
 

@@ -222,7 +222,7 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
   net->off_dens = a.take(sizeof(uint64_t) * batch * F);
   // the two sets of compaction look-back statuses
   net->off_tiles = a.take(sizeof(uint32_t) * 2 * kMaxTiles);
-  net->off_se_par = a.take(sizeof(int));
+  net->off_se_par = a.take(2 * sizeof(int));
   net->off_xhat = a.take((size_t)t0.grid * in_c * net->esize);
   // Per-site buffers of the emitted tensors and rulebooks hold F frames
   // (chunk items: frame t's sites follow frame t-1's); the state, X_hat and
@@ -258,7 +258,6 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
     // pooled and (exact) squeeze-excitation layers keep their affected
     // list apart from their emitted rows; with frozen gates a
     // squeeze-excitation layer emits at its affected sites like any other
-    // (its reference pass still defers the update, so it keeps dP)
     if (L.pool || (L.se && !frozen_se)) {
       L.cnt_O = 2 * (L_n + 1) + L_n + i;
       L.off_O = a.take(sizeof(int32_t) * citems);
@@ -269,7 +268,6 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
       L.cnt_O = T.cnt_rows;
       L.off_O = T.off_rowpix;
       L.off_Mo = T.off_map;
-      if (L.se) L.off_dP = a.take(sizeof(float) * L.conv_grid * L.cout_p);
     }
     L.off_nbr = a.take(sizeof(int32_t) * citems * L.K);
     if (L.stateful)
@@ -344,15 +342,12 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
   net->off_part = a.take(std::max<size_t>(part_bytes, 256));
   net->n_cleanup = n_cleanup;
   net->off_cleanup = a.take(32 * n_cleanup);
-  // the reference frame keeps every pixel; without squeeze-excitation
-  // (whose gates need the per-image sums its own pass keeps) or residual
-  // carry (whose views its list pass rebuilds) it runs dense
-  net->dense_ref = !net->has_se && !carry;
-  if (net->dense_ref) {
-    net->off_refcnt = a.take(sizeof(uint64_t) * net->n_counters);
-    net->n_iota = L_n + 1;
-    net->off_iota = a.take(16 * (size_t)net->n_iota);
-  }
+  const size_t before_tables = (size_t)round_up(a.top, kAlign);
+  net->off_refcnt = a.take(sizeof(uint64_t) * net->n_counters);
+  net->n_iota = L_n + 1;
+  net->off_iota = a.take(16 * (size_t)net->n_iota);
+  if (net->has_se || carry)
+    net->static_extra = (size_t)round_up(a.top, kAlign) - before_tables;
   for (LayerPlan& L : net->layers) {
     // (output, offset) pairs whose input site lies inside the input grid
     const st_layer_desc& d = L.d;

@@ -109,3 +109,112 @@ def test_dense_residual(dtype, hw):
     size = F.conv2d(row.abs(), wd.abs(), bd.abs()) + row.abs()
     err = (out.permute(0, 3, 1, 2) - want).abs()
     assert bool((err <= 44 * 2.0 ** -24 * size + 1e-6).all())
+
+
+# (dtype, batch, H, W, C, k, s, se_mid): channels below, at and past the
+# vectors a block's threads share (65 of them: a ragged second block row),
+# widths around a strip's four pixels, one pixel, both windows and strides
+DW_CASES = [
+    ("bf16", 1, 1, 1, 8, 3, 1, 0),
+    ("f16", 2, 5, 3, 24, 5, 1, 3),
+    ("f32", 1, 9, 13, 40, 3, 2, 5),
+    ("bf16", 3, 12, 17, 144, 5, 2, 6),
+    ("f16", 1, 33, 34, 520, 3, 1, 8),
+    ("f32", 2, 7, 9, 1152, 5, 1, 48),
+    ("bf16", 1, 70, 131, 32, 3, 1, 8),
+    ("f32", 1, 11, 12, 16, 5, 2, 0),
+]
+
+
+@pytest.mark.parametrize("case", DW_CASES,
+                         ids=lambda c: "-".join(map(str, c)))
+def test_dense_depthwise(case):
+    from paper_2410_20790_amd import SparseTemNet
+    dtype, n, h, w, c, k, s, mid = case
+    print("depthwise", case, flush=True)
+    rng = np.random.default_rng(5)
+    L = LayerSpec(src=-1, c_in=c, c_out=c, k=(k, k), s=(s, s),
+                  p=(k // 2, k // 2), groups=c, act=2, se_mid=mid)
+    L.weight = to_storage(rng.normal(0, 1 / k, (c, 1, k, k)), dtype)
+    L.bias = to_storage(rng.normal(0, 1, (c,)), dtype)
+    if mid:
+        L.se_w1 = to_storage(rng.normal(0, c ** -0.5, (mid, c)), dtype)
+        L.se_b1 = to_storage(rng.normal(0, 0.1, (mid,)), dtype)
+        L.se_w2 = to_storage(rng.normal(0, mid ** -0.5, (c, mid)), dtype)
+        L.se_b2 = to_storage(rng.normal(0, 1, (c,)), dtype)
+    x = to_storage(rng.normal(0, 1, (n, h, w, c)), dtype)
+    net = SparseTemNet([L], n, h, w, c, dtype)
+    try:
+        out = net.encode_reference(
+            torch.from_numpy(x).to("cuda", net.tdtype)).cpu().double()
+    finally:
+        net.close()
+
+    def t(a):
+        return torch.from_numpy(a).double()
+    xd = t(x).permute(0, 3, 1, 2)
+    pre = F.conv2d(xd, t(L.weight), t(L.bias), s, k // 2, 1, c)
+    size = F.conv2d(xd.abs(), t(L.weight).abs(), t(L.bias).abs(), s, k // 2,
+                    1, c)
+    want = F.silu(pre)
+    # as test_dense_convolution; the gate is within f32 roundings of sums
+    # over at most 10^4 sites and 1152 channels, relative to their size
+    bound = 1.1 * (2 + k * k) * 2.0 ** -24 * size + 1e-6
+    if mid:
+        z = F.silu(want.mean((2, 3)) @ t(L.se_w1).T + t(L.se_b1))
+        g = torch.sigmoid(z @ t(L.se_w2).T + t(L.se_b2))[:, :, None, None]
+        want = want * g
+        bound = bound + 2e-5 * (want.abs() + 1e-2)
+    err = (out.permute(0, 3, 1, 2) - want).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+
+@pytest.mark.parametrize("kind", ["se", "se_carry", "se_frozen", "carry"])
+def test_reference_artefacts(kind):
+    """What the queries see after a reference frame, also after diff frames
+    left other lists: every pixel a kept candidate, the geometry's rulebook,
+    the rounded activations as rows and (residual carry) as views."""
+    from paper_2410_20790_amd import SparseTemNet
+    from paper_2410_20790_amd import binding as B
+    from parity_util import to_dev
+    from workloads import (efficientnet_mini_net, random_sparse_video,
+                           resnet_mini_net)
+    net = (resnet_mini_net if kind == "carry" else efficientnet_mini_net)(
+        dtype="f16")
+    frames = random_sparse_video(3, 2, 1, net.H, net.W, 3, 0.1, "f16")
+    g = SparseTemNet(net.layers, 1, net.H, net.W, 3, "f16",
+                     carry="carry" in kind, frozen_se=kind == "se_frozen")
+    try:
+        g.encode_reference(to_dev(frames[0], "f16"))
+        g.encode_diff(to_dev(frames[1], "f16"), [0.0] * (g.n_layers + 1))
+        g.encode_reference(to_dev(frames[1], "f16"))
+        shape = {-1: g.in_shape[1:3]}
+        for i, L in enumerate(net.layers):
+            _, H, W, C = g.tensor_shape(i)
+            shape[i] = (H, W)
+            every = np.arange(H * W)
+            pix, rows = B.st_debug_candidates(g.handle, i, C)
+            np.testing.assert_array_equal(pix, every)
+            np.testing.assert_array_equal(B.st_debug_active(g.handle, i),
+                                          every)
+            hi, wi = shape[L.src]
+            ho = (hi + 2 * L.p[0] - L.k[0]) // L.s[0] + 1
+            wo = (wi + 2 * L.p[1] - L.k[1]) // L.s[1] + 1
+            want = [(k, iy * wi + ix, oy * wo + ox)
+                    for k in range(L.k[0] * L.k[1])
+                    for oy in range(ho) for ox in range(wo)
+                    for iy in [oy * L.s[0] - L.p[0] + k // L.k[1]]
+                    for ix in [ox * L.s[1] - L.p[1] + k % L.k[1]]
+                    if 0 <= iy < hi and 0 <= ix < wi]
+            got = B.st_debug_rulebook(g.handle, i)
+            np.testing.assert_array_equal(np.asarray(got, np.int64),
+                                          np.asarray(want, np.int64))
+            if L.act == 1 and not L.pool_k[0] and i + 1 < g.n_layers:
+                P = B.st_debug_state(g.handle, i, (1, H, W, C))
+                np.testing.assert_array_equal(
+                    rows, to_storage(np.maximum(P, 0), "f16").reshape(-1, C))
+            if "carry" in kind:
+                V = B.st_debug_carry(g.handle, i, (1, H, W, C))
+                np.testing.assert_array_equal(V.reshape(-1, C), rows)
+    finally:
+        g.close()
