@@ -363,6 +363,7 @@ bool run_layer(st_net* net, int i, float thr, const float* thr_dev,
     pa.rowmax = rowmax_out;
     pa.cp = L.cout_p;
     pa.act = d.act;
+    pa.tps = se_threads_per_site(L.cout_p);
     pa.yhat = net->carry ? ws.at<float>(L.off_yhat) : nullptr;
     launch_pool_emit(pf, s, net->dtype, pa);
     launch_commit(pf, s, O, cO, L.conv_grid, ws.at<float>(L.off_P),
@@ -503,7 +504,7 @@ static st_status encode_reference(st_net* net, const void* frame, float* out,
   // device memory, so that a captured frame replays correctly)
   if (net->has_se) launch_flip_parity(s, ws.at<int>(net->off_se_par));
   launch_iota_lists(pf, s, ws.at<IotaEntry>(net->off_iota), net->n_iota,
-                    net->ws, net->max_grid);
+                    net->iota_blocks, net->ws);
   launch_ref_counters(s, cnt, ws.at<u64>(net->off_refcnt), net->n_counters,
                       ws.at<int>(net->off_se_par) + 1);
   // online adjustment: every cycle_refs-th reference frame starts a new cycle
@@ -579,7 +580,7 @@ st_status encode(st_net* net, const void* frame, const float* thr, float* out,
   if (net->has_se && !net->frozen_se)
     launch_flip_parity(s, ws.at<int>(net->off_se_par));
   launch_cleanup(pf, s, ws.at<CleanEntry>(net->off_cleanup), net->n_cleanup,
-                 net->ws, cnt, net->max_grid);
+                 net->cleanup_blocks, net->ws, cnt);
   // online adjustment: after a diff frame encoded with the device
   // thresholds, one bisection step
   if (thr_dev) launch_ibst_step(s, cnt, 1, ibst_args(net));
@@ -899,7 +900,7 @@ st_status encode_chunk(st_net* net, const void* frames, int nf,
                          i == nl - 1 ? out : nullptr, s))
       return fail(net, ST_ERR_HIP, "internal: GEMM launch arguments");
   launch_cleanup(pf, s, ws.at<CleanEntry>(net->off_cleanup), net->n_cleanup,
-                 net->ws, cnt, net->max_grid);
+                 net->cleanup_blocks, net->ws, cnt);
   // exact squeeze-excitation: the chunk's last gates (in the new slots)
   // become the previous ones
   if (net->has_se && !net->frozen_se)
@@ -968,16 +969,20 @@ extern "C" st_status st_bind_workspace(st_net* net, void* dev_ptr,
   for (const TensorPlan& T : net->tensors)
     launch_fill_u32(s, ws.at<int>(T.off_map), T.grid * net->F, 0xFFFFFFFFu);
   std::vector<CleanEntry> tab;
+  net->cleanup_blocks = net->iota_blocks = 0;
+  auto clean = [&](size_t map, size_t list, int cnt, int64_t cap) {
+    tab.push_back(CleanEntry{(int64_t)map, (int64_t)list, cnt,
+                             net->cleanup_blocks, 0});
+    net->cleanup_blocks += table_blocks(cap, 4096);
+  };
   for (const TensorPlan& T : net->tensors)
-    tab.push_back(CleanEntry{(int64_t)T.off_map, (int64_t)T.off_rowpix,
-                             T.cnt_rows, 0, 0});
+    clean(T.off_map, T.off_rowpix, T.cnt_rows, T.grid * net->F);
   for (const LayerPlan& L : net->layers) {
     const st_layer_desc& d = L.d;
     if (L.pool || (L.se && !net->frozen_se)) {
       launch_fill_u32(s, ws.at<int>(L.off_Mo), L.conv_grid * net->F,
                       0xFFFFFFFFu);
-      tab.push_back(CleanEntry{(int64_t)L.off_Mo, (int64_t)L.off_O, L.cnt_O,
-                               0, 0});
+      clean(L.off_Mo, L.off_O, L.cnt_O, L.conv_grid * net->F);
     }
     if (L.se) {
       launch_to_f32_pad(s, net->dtype, d.se_w1, ws.at<float>(L.off_sew1),
@@ -1019,7 +1024,9 @@ extern "C" st_status st_bind_workspace(st_net* net, void* dev_ptr,
     keep_iota.clear();
     for (const TensorPlan& T : net->tensors) {
       keep_cnt[T.cnt_rows] = keep_cnt[T.cnt_act] = (u64)T.grid;
-      keep_iota.push_back(IotaEntry{(int64_t)T.off_act, T.grid});
+      keep_iota.push_back(IotaEntry{(int64_t)T.off_act, (int32_t)T.grid,
+                                    net->iota_blocks});
+      net->iota_blocks += table_blocks(T.grid, 8192);
     }
     for (const LayerPlan& L : net->layers) {
       keep_cnt[L.cnt_O] = (u64)L.conv_grid;

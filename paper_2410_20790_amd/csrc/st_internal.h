@@ -158,8 +158,8 @@ struct st_net {
   size_t off_refcnt = 0, off_iota = 0;
   size_t off_dens = 0;                     // uint64 [batch] per-image counts
   int n_counters = 0;
-  int n_cleanup = 0;
-  int n_iota = 0;
+  int n_cleanup = 0, cleanup_blocks = 0;   // table entries, launch blocks
+  int n_iota = 0, iota_blocks = 0;
   int64_t max_grid = 0;
   // runtime
   char* ws = nullptr;

@@ -18,9 +18,16 @@ struct Geo {  // sliding-window geometry from an input grid to an output grid
 
 struct CleanEntry {  // map[list[r]] = -1 for r < counter[cnt]
   int64_t map_off, list_off;
-  int32_t cnt, pad;
-  int64_t pad2;
+  int32_t cnt;
+  int32_t first;  // first block of the launch that works on it
+  int64_t pad;
 };
+// Blocks of a table launch that work on an entry of n items, `per` items a
+// block at least.
+inline int table_blocks(int64_t n, int64_t per) {
+  const int64_t b = (n + per - 1) / per;
+  return (int)(b < 1 ? 1 : b > 256 ? 256 : b);
+}
 
 using u64 = unsigned long long;
 
@@ -46,10 +53,11 @@ void launch_dense_input(const Prof& pf, hipStream_t s, int dtype,
                         const void* x, void* xhat, void* rows, int C, int Cp,
                         int64_t npix);
 struct IotaEntry {  // list[r] = r for r < n
-  int64_t off, n;
+  int64_t off;
+  int32_t n, first;  // first: as in CleanEntry
 };
 void launch_iota_lists(const Prof& pf, hipStream_t s, const IotaEntry* tab,
-                       int n_tab, char* ws, int64_t max_n);
+                       int n_tab, int blocks, char* ws);
 void launch_ref_counters(hipStream_t s, u64* dst, const u64* src, int n,
                          int* last_ref);
 // dense max-pool emission of the reference pass: pooled row q (pixel
@@ -59,7 +67,7 @@ void launch_pool_dense(const Prof& pf, hipStream_t s, int dtype,
                        const float* P, int p16, void* dout, float* ynew,
                        Geo g, int cp, int act, int64_t nq);
 void launch_cleanup(const Prof& pf, hipStream_t s, const CleanEntry* tab,
-                    int n_tab, char* ws, const u64* cnt, int64_t max_rows);
+                    int n_tab, int blocks, char* ws, const u64* cnt);
 
 // ---- consumer-side rulebook preparation (done while a tensor's kept rows
 // are emitted)
@@ -248,6 +256,7 @@ struct PoolArgs {
   void* dout;
   uint32_t* rowmax;
   int cp, act;
+  int tps;             // lanes per pooled row (a power of two, at most 64)
   const float* yhat;    // residual carry view (pooled grid) or NULL
 };
 void launch_pool_emit(const Prof& pf, hipStream_t s, int dtype,

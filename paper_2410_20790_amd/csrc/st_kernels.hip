@@ -2456,48 +2456,85 @@ void launch_conv_dw(const Prof& pf, hipStream_t s, int dtype,
 // ----------------------------------------------------------- max-pool
 // Delta of a pooled output = max over its window of f(P_new) minus the
 // same max of f(P_old); P_new = P_old + dP on affected conv outputs.
-template <typename T>
-__global__ __launch_bounds__(256) void k_pool_emit(PoolArgs a) {
+// `tps` adjacent lanes (a power of two, at most a wave) take a pooled row, 8
+// channels at a time, so a row's maximum is a shuffle and one plain store
+// (one thread and one device atomic per element: 50 us per layer of CRNN-VGG,
+// now 5 us).  The window's sites go four at a time: their map entries, then
+// their states and updates, are requested together.
+template <typename T, int ACT>
+__device__ __forceinline__ void pool_emit_rows(const PoolArgs& a) {
   T* dout = (T*)a.dout;
   const int64_t nQ = (int64_t)*a.nQ;
-  const int64_t total = nQ * a.cp;
   const Geo& g = a.g;  // Hi/Wi: conv grid, Ho/Wo: pooled grid
-  const int64_t hwq = (int64_t)g.Ho * g.Wo;
-  for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < total;
-       idx += (int64_t)gridDim.x * 256) {
-    const int64_t q = idx / a.cp;
-    const int c = (int)(idx - q * a.cp);
-    const int p = a.Q[q];
-    const int n = (int)(p / hwq);
-    const int rem = (int)(p - n * hwq);
-    const int qy = rem / g.Wo, qx = rem - (rem / g.Wo) * g.Wo;
-    float mo = -INFINITY, mn = -INFINITY;
-    for (int ky = 0; ky < g.kh; ++ky) {
-      const int iy = qy * g.sh - g.ph + ky;
-      if (iy < 0 || iy >= g.Hi) continue;
-      for (int kx = 0; kx < g.kw; ++kx) {
-        const int ix = qx * g.sw - g.pw + kx;
-        if (ix < 0 || ix >= g.Wi) continue;
-        const int64_t w = ((int64_t)n * g.Hi + iy) * g.Wi + ix;
-        const float po = a.P[w * a.cp + c];
-        const int r = a.Mo[w];
-        const float pn = r >= 0 ? po + a.dP[(int64_t)r * a.cp + c] : po;
-        mo = fmaxf(mo, act_f(po, a.act));
-        mn = fmaxf(mn, act_f(pn, a.act));
+  const unsigned hwq = (unsigned)g.Ho * (unsigned)g.Wo;
+  const int lane = threadIdx.x % a.tps, R = 256 / a.tps;
+  const int V = a.cp / 8, KW = g.kh * g.kw;
+  // whole groups leave the loop together, so the shuffles see their lanes
+  for (int64_t q = (int64_t)blockIdx.x * R + threadIdx.x / a.tps; q < nQ;
+       q += (int64_t)gridDim.x * R) {
+    const unsigned p = (unsigned)a.Q[q];
+    const unsigned n = p / hwq, rem = p - n * hwq;
+    const int qy = (int)(rem / (unsigned)g.Wo);
+    const int qx = (int)rem - qy * g.Wo;
+    float rm = 0.f;
+    for (int v = lane; v < V; v += a.tps) {
+      const int c0 = v * 8;
+      float mo[8], mn[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mo[e] = mn[e] = -INFINITY;
+      for (int k0 = 0; k0 < KW; k0 += 4) {
+        int64_t w[4];
+        int r[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = k0 + u, ky = k / g.kw;
+          const int iy = qy * g.sh - g.ph + ky;
+          const int ix = qx * g.sw - g.pw + k - ky * g.kw;
+          const bool in = k < KW && iy >= 0 && iy < g.Hi && ix >= 0 &&
+                          ix < g.Wi;
+          w[u] = in ? ((int64_t)n * g.Hi + iy) * g.Wi + ix : -1;
+          r[u] = in ? a.Mo[w[u]] : -1;
+        }
+        float po[4][8], dp[4][8];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) po[u][e] = dp[u][e] = 0.f;
+          if (w[u] >= 0) load8f(a.P + w[u] * a.cp + c0, po[u]);
+          if (r[u] >= 0) load8f(a.dP + (int64_t)r[u] * a.cp + c0, dp[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (w[u] < 0) continue;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            mo[e] = fmaxf(mo[e], act_c<ACT>(po[u][e]));
+            mn[e] = fmaxf(mn[e], act_c<ACT>(r[u] >= 0 ? po[u][e] + dp[u][e]
+                                                      : po[u][e]));
+          }
+        }
       }
+      // residual carry: against what the consumers received
+      if (a.yhat) load8f(a.yhat + (int64_t)p * a.cp + c0, mo);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) mn[e] -= mo[e];
+      rm = fmaxf(rm, Vec8<T>::store(dout + q * a.cp + c0, mn));
     }
-    // residual carry: against what the consumers received
-    if (a.yhat) mo = a.yhat[(int64_t)p * a.cp + c];
-    const T qv = from_f<T>(mn - mo);
-    dout[q * a.cp + c] = qv;
-    const float ab = fabsf(to_f(qv));
-    if (ab > 0.f) atomicMax(a.rowmax + q, __float_as_uint(ab));
+    for (int o = 1; o < a.tps; o <<= 1) rm = fmaxf(rm, __shfl_xor(rm, o, 64));
+    if (lane == 0) a.rowmax[q] = __float_as_uint(rm);
   }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_pool_emit(PoolArgs a) {
+  with_act(a.act, [&](auto act_tag) {
+    pool_emit_rows<T, decltype(act_tag)::value>(a);
+  });
 }
 
 void launch_pool_emit(const Prof& pf, hipStream_t s, int dtype,
                       const PoolArgs& a) {
-  const int grid = grid_for(a.capQ * a.cp, 8192);
+  const int grid = grid_for(a.capQ * a.tps, 4096);
   prof_begin(pf, 12 /*ST_K_POOL_EMIT*/, s);
   if (dtype == 0)
     k_pool_emit<float><<<grid, 256, 0, s>>>(a);
@@ -3920,22 +3957,40 @@ void launch_reset(const Prof& pf, hipStream_t s, u64* cnt, int n,
   prof_end(pf, 18, s);
 }
 
+// A table launch gives every entry blocks by its capacity (the same count for
+// all kept 25,000 blocks, most without work, busy for 12 us of a ResNet-50
+// frame).  This block's entry: the last whose first block is not past it
+// (each wave counts them, 64 at a time).
+template <class E>
+__device__ __forceinline__ int table_entry(const E* tab, int n_tab) {
+  int n = 0;
+  for (int base = 0; base < n_tab; base += 64) {
+    const int i = base + (int)(threadIdx.x & 63);
+    const u64 m = __ballot(i < n_tab && tab[i].first <= (int)blockIdx.x);
+    n += __popcll(m);
+    if (m != ~0ull) break;
+  }
+  return n - 1;
+}
+
 __global__ __launch_bounds__(256) void k_cleanup(const CleanEntry* tab,
-                                                 char* ws, const u64* cnt) {
-  const CleanEntry e = tab[blockIdx.y];
+                                                 int n_tab, char* ws,
+                                                 const u64* cnt) {
+  const int t = table_entry(tab, n_tab);
+  const CleanEntry e = tab[t];
+  const int last = t + 1 < n_tab ? tab[t + 1].first : (int)gridDim.x;
   int* map = (int*)(ws + e.map_off);
   const int* list = (const int*)(ws + e.list_off);
   const int64_t n = (int64_t)cnt[e.cnt];
-  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < n;
-       r += (int64_t)gridDim.x * 256)
+  for (int64_t r = (int64_t)((int)blockIdx.x - e.first) * 256 + threadIdx.x;
+       r < n; r += (int64_t)(last - e.first) * 256)
     map[list[r]] = -1;
 }
 
 void launch_cleanup(const Prof& pf, hipStream_t s, const CleanEntry* tab,
-                    int n_tab, char* ws, const u64* cnt, int64_t max_rows) {
+                    int n_tab, int blocks, char* ws, const u64* cnt) {
   prof_begin(pf, 17 /*ST_K_CLEANUP*/, s);
-  dim3 grid(grid_for(max_rows, 512), n_tab);
-  k_cleanup<<<grid, 256, 0, s>>>(tab, ws, cnt);
+  k_cleanup<<<blocks, 256, 0, s>>>(tab, n_tab, ws, cnt);
   prof_end(pf, 17, s);
 }
 
@@ -3978,20 +4033,27 @@ void launch_dense_input(const Prof& pf, hipStream_t s, int dtype,
 }
 
 __global__ __launch_bounds__(256) void k_iota_lists(const IotaEntry* tab,
-                                                    char* ws) {
-  const IotaEntry e = tab[blockIdx.y];
+                                                    int n_tab, char* ws) {
+  const int t = table_entry(tab, n_tab);
+  const IotaEntry e = tab[t];
+  const int last = t + 1 < n_tab ? tab[t + 1].first : (int)gridDim.x;
   int* list = (int*)(ws + e.off);
-  for (int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x; r < e.n;
-       r += (int64_t)gridDim.x * 256)
-    list[r] = (int)r;
+  // four entries per store (the lists are 256-byte aligned)
+  for (int64_t r = ((int64_t)((int)blockIdx.x - e.first) * 256 +
+                    threadIdx.x) * 4;
+       r < e.n; r += (int64_t)(last - e.first) * 1024) {
+    if (r + 4 <= e.n)
+      *(int4*)(list + r) = make_int4((int)r, (int)r + 1, (int)r + 2,
+                                     (int)r + 3);
+    else
+      for (int64_t i = r; i < e.n; ++i) list[i] = (int)i;
+  }
 }
 
 void launch_iota_lists(const Prof& pf, hipStream_t s, const IotaEntry* tab,
-                       int n_tab, char* ws, int64_t max_n) {
-  if (n_tab < 1) return;
-  const dim3 grid(grid_for(max_n, 1024), n_tab);
+                       int n_tab, int blocks, char* ws) {
   prof_begin(pf, 17 /*ST_K_CLEANUP*/, s);
-  k_iota_lists<<<grid, 256, 0, s>>>(tab, ws);
+  k_iota_lists<<<blocks, 256, 0, s>>>(tab, n_tab, ws);
   prof_end(pf, 17, s);
 }
 
