@@ -27,6 +27,7 @@ SOURCES = [
     ("st_plan.cpp", []),
     ("st_kernels.hip", DEVICE),
     ("st_dense.hip", DEVICE),
+    ("st_gather.hip", DEVICE),
     ("st_exec.hip", DEVICE),
 ]
 

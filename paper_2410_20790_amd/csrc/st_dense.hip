@@ -37,34 +37,18 @@
 
 #include "st_device.h"
 #include "st_kernels.h"
+#include "st_stage.h"
 
 namespace st {
 
 namespace {
 
-constexpr int kRowBytes = 128;  // a staged row: 64 half or 32 f32 columns
 constexpr int kDenseXcd = 8;
 
 // Which input rows an offset reads: a 1x1 kernel has one row per pixel; with
 // a channel count that is a multiple of the stage's columns a stage lies
 // within one offset; otherwise every lane walks its own (offset, channel).
 enum { kSrcPoint = 0, kSrcAligned = 1, kSrcAny = 2 };
-
-__device__ __forceinline__ void load_to_lds(const void* g, char* lds) {
-  __builtin_amdgcn_global_load_lds(
-      (__attribute__((address_space(1))) const uint32_t*)(uintptr_t)g,
-      (__attribute__((address_space(3))) uint32_t*)lds, 16, 0, 0);
-}
-
-// Wait until at most N of this wave's vector-memory operations are
-// outstanding (and its LDS reads are done), then meet the block's waves.
-template <int N>
-__device__ __forceinline__ void stage_ready() {
-  static_assert(N < 64, "vmcnt");
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 // One thread's share of the staged loads: PQ pixel vectors and WQ weight
 // vectors per stage.
@@ -164,68 +148,6 @@ struct DenseLoader {
     }
   }
 };
-
-// One stage's products from the stage buffer: WM pixels (in blocks of 16,
-// from row pr) by WN channels (weight rows from wr).
-template <typename T, int IM, int JN>
-__device__ __forceinline__ void stage_products(const char* buf, int pr,
-                                               int wr, int l16, int lg,
-                                               v4f (&acc)[IM][JN]) {
-#pragma unroll
-  for (int kk = 0; kk < 2; ++kk) {
-    const int slot = ((kk * 4 + lg) ^ (l16 & 7)) * 16;
-    uint4 pv[IM], wv[JN];
-#pragma unroll
-    for (int i = 0; i < IM; ++i)
-      pv[i] = *(const uint4*)(buf + (pr + i * 16 + l16) * kRowBytes + slot);
-#pragma unroll
-    for (int j = 0; j < JN; ++j)
-      wv[j] = *(const uint4*)(buf + (wr + (j >> 1) * 32 + (l16 >> 2) * 8 +
-                                     (j & 1) * 4 + (l16 & 3)) *
-                                        kRowBytes +
-                              slot);
-#pragma unroll
-    for (int i = 0; i < IM; ++i) {
-#pragma unroll
-      for (int j = 0; j < JN; ++j) {
-        if constexpr (sizeof(T) == 4) {
-          const float4 w = __builtin_bit_cast(float4, wv[j]);
-          const float4 p = __builtin_bit_cast(float4, pv[i]);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.x, p.x,
-                                                           acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.y, p.y,
-                                                           acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.z, p.z,
-                                                           acc[i][j], 0, 0, 0);
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(w.w, p.w,
-                                                           acc[i][j], 0, 0, 0);
-        } else if constexpr (__is_same(T, _Float16)) {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-              __builtin_bit_cast(v8h, wv[j]), __builtin_bit_cast(v8h, pv[i]),
-              acc[i][j], 0, 0, 0);
-        } else {
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              __builtin_bit_cast(v8bf, wv[j]), __builtin_bit_cast(v8bf, pv[i]),
-              acc[i][j], 0, 0, 0);
-        }
-      }
-    }
-  }
-}
-
-// One turn of the stage ring: stage `rd` has arrived once at most AHEAD
-// later loads of this wave are outstanding; the loads of the stage S - 1
-// ahead go to `wr`, which every wave finished reading before the barrier.
-template <typename T, int BM, int AHEAD, int IM, int JN, class Loader>
-__device__ __forceinline__ void stage_turn(const ConvArgs& a, Loader& ld,
-                                           const char* __restrict__ rd,
-                                           char* __restrict__ wr, int pr,
-                                           int wrow, int l16, int lg,
-                                           v4f (&acc)[IM][JN]) {
-  stage_ready<AHEAD>();
-  ld.template issue<BM>(a, wr);
-  stage_products<T, IM, JN>(rd, pr, wrow, l16, lg, acc);
-}
 
 // Tile of BM pixels by BN channels in waves of WM by WN, S stages in LDS.
 // SPLIT: block row y reduces its part of the stages and writes f32 partial
@@ -403,7 +325,9 @@ void dense_launch(hipStream_t s, const ConvArgs& a, int splits = 1) {
 //    128x32 for at most 32 channels, where half of a 64-channel tile would
 //    be padding.
 // With fewer than 128 tiles of 64x64 a long reduction is split, enough for
-// about 256 blocks, at least 8 stages each.
+// about 256 blocks, at least 8 stages each (f32, whose products bound it and
+// whose sums the shorter chains keep closer: under 1024 tiles, enough for
+// 1024 blocks, at least 4 stages).
 template <typename T>
 int dense_conv(hipStream_t s, const ConvArgs& a) {
   constexpr int KC = kRowBytes / (int)sizeof(T);
@@ -427,10 +351,12 @@ int dense_conv(hipStream_t s, const ConvArgs& a) {
     return 1;
   }
   int splits = 1;
-  if (a.split_max > 1 && m64 * n64 < 128) {
-    splits = (int)((256 + m64 * n64 - 1) / (m64 * n64));
+  constexpr int kBlocks = sizeof(T) == 4 ? 1024 : 256;
+  constexpr int kStages = sizeof(T) == 4 ? 4 : 8;
+  if (a.split_max > 1 && m64 * n64 < (sizeof(T) == 4 ? 1024 : 128)) {
+    splits = (int)((kBlocks + m64 * n64 - 1) / (m64 * n64));
     splits = splits < a.split_max ? splits : a.split_max;
-    splits = splits < nst / 8 ? splits : nst / 8;
+    splits = splits < nst / kStages ? splits : nst / kStages;
   }
   if (splits > 1) {
     dense_launch<T, 64, 64, 32, 32, 4, true>(s, a, splits);

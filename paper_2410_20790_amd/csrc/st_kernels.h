@@ -238,6 +238,17 @@ inline bool dense_dw_takes(const ConvArgs& a) {
 }
 void launch_dense_dw(const Prof& pf, hipStream_t s, int dtype,
                      const ConvArgs& a, int images);
+// The gathered convolutions of a diff frame or a chunk that st_gather.hip
+// takes: 1x1 kernels and windows of up to nine offsets over channel counts
+// that fill whole stages (64 half-precision or 32 f32 columns), in every
+// mode but a pooled layer's chunk.  An f32 net with a bf16 state keeps the
+// other kernel's order of sums (see dense_conv_takes).
+inline bool gather_takes(int dtype, const ConvArgs& a) {
+  const int kc = dtype == 0 ? 32 : 64;
+  return a.mode != kModeChunkPool && !(dtype == 0 && a.p16) &&
+         (a.K == 1 ? a.cin_p % 8 == 0 : a.K <= 9 && a.cin_p % kc == 0);
+}
+void launch_gather_conv(hipStream_t s, int dtype, const ConvArgs& a);
 // Returns false (and launches nothing) when a.zero is missing or misaligned.
 bool launch_conv_gemm(const Prof& pf, hipStream_t s, int dtype,
                       const ConvArgs& a);

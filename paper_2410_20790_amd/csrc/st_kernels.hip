@@ -24,6 +24,7 @@
 
 #include "st_device.h"
 #include "st_kernels.h"
+#include "st_stage.h"
 
 namespace st {
 
@@ -43,12 +44,6 @@ __device__ __forceinline__ unsigned block_sum(unsigned v) {
   if ((threadIdx.x & 63) == 0) red[w] = v;
   __syncthreads();
   return red[0] + red[1] + red[2] + red[3];
-}
-
-__device__ __forceinline__ unsigned lane_prefix(u64 ballot) {
-  return __builtin_amdgcn_mbcnt_hi((unsigned)(ballot >> 32),
-                                   __builtin_amdgcn_mbcnt_lo((unsigned)ballot,
-                                                             0u));
 }
 
 __device__ __forceinline__ int64_t read_count(const u64* dev, int64_t host) {
@@ -746,19 +741,6 @@ __device__ __forceinline__ int gemm_stages(const ConvArgs& a) {
   return min((int)a.ktot_p, (a.K * a.cin_p + KC - 1) / KC * KC) / KC;
 }
 
-// Splits of the reduction per output tile for this frame: enough work units
-// (tiles x splits) to give every CU several, at most split_max, and at
-// least kSplitMinStages stages per split.  The GEMM and its split epilogue
-// both derive it from the same device count.
-constexpr int kSplitTarget = 1024, kSplitMinStages = 4;
-__device__ __forceinline__ int split_count(int64_t ntiles, int nst, int smax) {
-  if (smax <= 1 || ntiles <= 0) return 1;
-  int64_t sp = (kSplitTarget + ntiles - 1) / ntiles;
-  sp = min(sp, (int64_t)smax);
-  sp = min(sp, (int64_t)max(1, nst / kSplitMinStages));
-  return (int)max(sp, (int64_t)1);
-}
-
 // Finishes one thread's share of an output tile -- row eo of the tile,
 // columns n0 + ec + [0, 16) -- from the reduced values v: adds the bias
 // (reference pass) and the residual delta, then either defers the update
@@ -857,27 +839,6 @@ __device__ __forceinline__ void finish_tile(const ConvArgs& a, LoadV load_v,
   const float rm = finish_cols<T, REF, ACT>(a, load_v, load_po, load_sk, hv,
                                             eo, epix, n0, ec);
   finish_rows(a, rm, eo, eok);
-}
-
-// Four channels of a delta row stored in the storage type; returns the
-// largest magnitude of the rounded values (the rounded largest magnitude,
-// as rounding to nearest is monotone and odd).
-template <typename T>
-__device__ __forceinline__ float store4(T* p, const float* f) {
-  float m = 0.f;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) m = fmaxf(m, fabsf(f[e]));
-  if constexpr (sizeof(T) == 4) {
-    *(float4*)p = make_float4(f[0], f[1], f[2], f[3]);
-    return m;
-  } else {
-    uint2 v;
-    T* h = (T*)&v;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) h[e] = from_f<T>(f[e]);
-    *(uint2*)p = v;
-    return to_f(from_f<T>(m));
-  }
 }
 
 // Chunk-state epilogue, for CPT columns per thread (64 / CPT threads per
@@ -1108,13 +1069,6 @@ template <typename T> struct GemmTile {
   static constexpr int IM = WM / 16, JN = WN / 16;
   static constexpr int BLOCKS_PER_CU = 4;
 };
-
-// Reduction stages of a layer that hold real (not padding) columns, for
-// stages of KC columns.
-template <int KC>
-__device__ __forceinline__ int gemm_stages_kc(const ConvArgs& a) {
-  return min((int)a.ktot_p, (a.K * a.cin_p + KC - 1) / KC * KC) / KC;
-}
 
 // SPLIT: the layer's reduction may be split (split_max > 1); every unit
 // then writes its partial tile (even when this frame needs one split) and
@@ -2296,6 +2250,13 @@ bool launch_conv_gemm(const Prof& pf, hipStream_t s, int dtype,
     prof_begin(pf, 7 /*ST_K_CONV_GEMM*/, s);
     fn<<<grid, 256, lds, s>>>(a);
     prof_end(pf, 7, s);
+    return true;
+  }
+  if (!a.dense && gather_takes(dtype, a)) {
+    prof_begin(pf, 7 /*ST_K_CONV_GEMM*/, s);
+    launch_gather_conv(s, dtype, a);
+    prof_end(pf, 7, s);
+    if (a.split_max > 1) split_epilogue(pf, s, dtype, a, 0);
     return true;
   }
   const int rstep = a.tstart ? chunk_tile_step(a.nf) : kGemmBM;
