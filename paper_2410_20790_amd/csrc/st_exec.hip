@@ -790,9 +790,6 @@ bool run_layer_chunk(st_net* net, int i, int nf, float thr,
     c.nchunk = L.se_nchunk;
     c.tps = L.se_tps;
     launch_chunk_se(pf, s, net->dtype, c, se_args(net, i));
-    launch_chunk_commit(pf, s, c.p16, ws.at<float>(L.off_P), cdp, O, cO,
-                        ws.at<uint32_t>(net->off_chunk_aff), citems,
-                        L.conv_grid, L.cout_p);
   }
   if (L.pool) {
     const Geo gp = pool_geo(L);

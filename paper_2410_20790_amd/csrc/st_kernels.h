@@ -345,10 +345,12 @@ void launch_se(const Prof& pf, hipStream_t s, int dtype, const SeArgs& a);
 // site * nf + t.  Finally the last frame's gates go to the new gate slot.
 struct ChunkSeArgs {
   int p16;
-  const float* P;       // state before the chunk [npix][cp]
+  float* P;             // state before the chunk [npix][cp]; the emission
+                        // stores the last one
   const float* Pt;      // per-item states after their frame's update
   const int* Mo;        // conv item (frame * npix + site) -> Pt row or -1
-  const uint32_t* aff;  // [npix] frames that updated each site
+  uint32_t* aff;        // [npix] frames that updated each site (cleared by
+                        // the emission)
   float* part;          // [nf][N][nchunk][cp]
   float* gates;         // [nf][N][cp]
   float* slots;         // the layer's two gate slots [2][N][cp]

@@ -2674,6 +2674,7 @@ __global__ __launch_bounds__(256) void k_se_squeeze(SeArgs a) {
 // of its partials, which only this block reads.
 constexpr int kSeMeanVecs = 2048;  // lane sums a block holds
 constexpr int kSeMeanTots = 512;   // and channel sums
+constexpr int kSeMeanFrames = 8;   // and frames at most
 __global__ void k_se_means(SeArgs a, int lanes, int cols, int fb) {
   __shared__ float4 red[kSeMeanVecs];
   __shared__ float tot[kSeMeanTots];
@@ -2688,35 +2689,63 @@ __global__ void k_se_means(SeArgs a, int lanes, int cols, int fb) {
   if (owner && !a.ref) sum = *S;
   for (int f0 = 0; f0 < nfr; f0 += fb) {
     const int nb = min(fb, nfr - f0);
-    for (int f = 0; f < nb; ++f) {
-      const float4* part = (const float4*)(a.part +
-                                           (f0 + f) * a.part_stride +
-                                           (int64_t)n * a.nchunk * cp);
-      float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (v < V4 && l < lanes) {
-#pragma unroll 8
-        for (int g = l; g < a.nchunk; g += lanes) {
-          const float4 q = part[(int64_t)g * V4 + v];
-          acc.x += q.x; acc.y += q.y; acc.z += q.z; acc.w += q.w;
+    // (every frame's partials of a chunk are requested together)
+    float4 acc[kSeMeanFrames];
+#pragma unroll
+    for (int f = 0; f < kSeMeanFrames; ++f)
+      acc[f] = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4* part =
+        (const float4*)(a.part + f0 * a.part_stride +
+                        (int64_t)n * a.nchunk * cp);
+    if (v < V4 && l < lanes)
+      for (int g0 = l; g0 < a.nchunk; g0 += 2 * lanes) {
+        float4 q[2][kSeMeanFrames];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int f = 0; f < kSeMeanFrames; ++f) {
+            // (parts and frames past the last one read the last)
+            const int g = min(g0 + j * lanes, a.nchunk - 1);
+            q[j][f] = part[min(f, nb - 1) * (a.part_stride / 4) +
+                           (int64_t)g * V4 + v];
+          }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          if (g0 + j * lanes >= a.nchunk) break;
+#pragma unroll
+          for (int f = 0; f < kSeMeanFrames; ++f) {
+            acc[f].x += q[j][f].x; acc[f].y += q[j][f].y;
+            acc[f].z += q[j][f].z; acc[f].w += q[j][f].w;
+          }
         }
       }
-      red[f * NT + tid] = acc;
-    }
+#pragma unroll
+    for (int f = 0; f < kSeMeanFrames; ++f)
+      if (f < nb) red[f * NT + tid] = acc[f];
     __syncthreads();
     for (int i = tid; i < nb * W; i += NT) {
       const int f = i / W, k = i - f * W;
       const float* r = (const float*)(red + f * NT) + k;
       float s = r[0];
+#pragma unroll 16
       for (int j = 1; j < lanes; ++j) s += r[W * j];
       tot[i] = s;
     }
     __syncthreads();
-    if (owner)
-      for (int f = 0; f < nb; ++f) {
-        sum += (double)tot[f * W + tid];
-        a.part[(f0 + f) * a.part_stride + (int64_t)n * a.nchunk * cp + c] =
-            (float)(sum / (double)a.hw);
+    if (owner) {
+      // the frames' sums first, then their divisions side by side
+      double at[kSeMeanFrames];
+#pragma unroll
+      for (int f = 0; f < kSeMeanFrames; ++f) {
+        if (f < nb) sum += (double)tot[f * W + tid];
+        at[f] = sum;
       }
+#pragma unroll
+      for (int f = 0; f < kSeMeanFrames; ++f)
+        if (f < nb)
+          a.part[(f0 + f) * a.part_stride + (int64_t)n * a.nchunk * cp + c] =
+              (float)(at[f] / (double)a.hw);
+    }
     // (the next turn writes red before its first barrier and tot after it)
   }
   if (owner) *S = sum;
@@ -2840,10 +2869,12 @@ static void se_excite(const Prof& pf, hipStream_t s, const SeArgs& a) {
   // channels of an image), and as many frames as the block's lane sums allow
   const int V4 = a.cp / 4, lanes = kSeExciteThreads / V4;
   const int cols = lanes >= 256 ? 1 : 256 / lanes > 16 ? 16 : 256 / lanes;
-  const int nt = (cols * lanes + 63) / 64 * 64;
-  const int by_red = kSeMeanVecs / nt, by_tot = kSeMeanTots / (4 * cols);
+  const int nt = cols * lanes > 256 ? 512 : 256;
+  int fb = kSeMeanVecs / nt;
+  if (fb > kSeMeanTots / (4 * cols)) fb = kSeMeanTots / (4 * cols);
+  if (fb > kSeMeanFrames) fb = kSeMeanFrames;
   k_se_means<<<dim3((V4 + cols - 1) / cols, a.N), nt, 0, s>>>(
-      a, lanes, cols, by_red < by_tot ? by_red : by_tot);
+      a, lanes, cols, fb);
   k_se_gates<<<dim3(a.N, a.nfr > 1 ? a.nfr : 1), kSeExciteThreads,
                sizeof(float) * (a.cp + round_up8(a.mid) +
                                 4 * kSeExciteThreads),
@@ -2882,11 +2913,21 @@ __global__ __launch_bounds__(256) void k_se_emit(SeArgs a) {
       const bool carry = a.yhat != nullptr;
       // residual carry: against what the consumers received
       load8f(carry ? a.yhat + row * cp + c0 : so + c0, go);
+      float fo[8], fn[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         pn[e] = state_round(a.p16, po[e] + dp[e]);
-        const float en = act_f(pn[e], a.act) * gn[e];
-        const float eo = carry ? go[e] : act_f(po[e], a.act) * go[e];
+        fo[e] = act_f(po[e], a.act);
+        fn[e] = fo[e];
+      }
+      if (r >= 0) {  // elsewhere the state, and so f, stays
+#pragma unroll
+        for (int e = 0; e < 8; ++e) fn[e] = act_f(pn[e], a.act);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float en = fn[e] * gn[e];
+        const float eo = carry ? go[e] : fo[e] * go[e];
         d[e] = en - eo;
       }
       rm = fmaxf(rm, Vec8<T>::store(dout + row * cp + c0, d));
@@ -3110,63 +3151,93 @@ __global__ __launch_bounds__(256) void k_chunk_se_squeeze(ChunkSeArgs a) {
   for (int c = threadIdx.x; c < cp; c += 256) part[c] = sm[c];
 }
 
-// Every site's frames in order (TPS lanes per site, its state in
-// registers): frame t's candidate row site * nf + t is
-// f(P_t) * s_t - f(P_{t-1}) * s_{t-1}.
-template <typename T, int TPS>
-__global__ __launch_bounds__(256) void k_chunk_se_emit(ChunkSeArgs a) {
-  constexpr int R = 256 / TPS, IT = TPS == 64 ? 4 : 1;
+// Every site's frames in order (TPS lanes per site): frame t's candidate row
+// site * nf + t is f(P_t) * s_t - f(P_{t-1}) * s_{t-1}.  The activation and
+// the gates of the frame before stay in registers: f is only evaluated where
+// a frame updated the site (evaluated twice per value and frame, its exp and
+// division bounded this pass: EfficientNet-B0's layers of 32 cameras 1430 us, now
+// 745).  The site's last state is committed here too, and its frame
+// bits cleared.
+template <typename T, int TPS, int ACT>
+__device__ __forceinline__ void chunk_se_emit_site(const ChunkSeArgs& a,
+                                                   int64_t p, int lane) {
+  constexpr int IT = TPS == 64 ? 4 : 1;
   T* dout = (T*)a.dout;
-  const int lane = threadIdx.x % TPS;
-  const int64_t p = (int64_t)blockIdx.x * R + threadIdx.x / TPS;
   const int cp = a.cp, V = cp / 8;
-  if (p < a.npix) {
-    const int n = (int)(p / a.hw);
-    const uint32_t bits = a.aff[p];
-    const float* g_first = gate_slot(a.slots, a.gpar, a.gsz, 0) +
-                           (int64_t)n * cp;
-    float pv[IT][8];
+  const int n = (int)(p / a.hw);
+  const uint32_t bits = a.aff[p];
+  const float* g_first =
+      gate_slot(a.slots, a.gpar, a.gsz, 0) + (int64_t)n * cp;
+  float fo[IT][8], go[IT][8];
+#pragma unroll
+  for (int k = 0; k < IT; ++k) {
+    const int v = lane + k * TPS;
+    if (v < V) {
+      state_load8(a.P, a.p16, p * cp + v * 8, fo[k]);
+      load8f(g_first + v * 8, go[k]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) fo[k][e] = act_c<ACT>(fo[k][e]);
+    }
+  }
+  int last = -1;
+  for (int t = 0; t < a.nf; ++t) {
+    const int r = ((bits >> t) & 1u) ? a.Mo[(int64_t)t * a.npix + p] : -1;
+    if (r >= 0) last = r;
+    const float* gn = a.gates + ((int64_t)t * a.N + n) * cp;
+    const int64_t j = p * a.nf + t;
+    float rm = 0.f;
 #pragma unroll
     for (int k = 0; k < IT; ++k) {
       const int v = lane + k * TPS;
-      if (v < V) state_load8(a.P, a.p16, p * cp + v * 8, pv[k]);
+      if (v >= V) break;
+      float fn[8], g1[8], d[8];
+      load8f(gn + v * 8, g1);
+      if (r >= 0) {
+        load8f(a.Pt + (int64_t)r * cp + v * 8, fn);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) fn[e] = act_c<ACT>(fn[e]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) fn[e] = fo[k][e];
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        d[e] = fn[e] * g1[e] - fo[k][e] * go[k][e];
+        fo[k][e] = fn[e];
+        go[k][e] = g1[e];
+      }
+      rm = fmaxf(rm, Vec8<T>::store(dout + j * cp + v * 8, d));
     }
-    for (int t = 0; t < a.nf; ++t) {
-      const int r = ((bits >> t) & 1u) ? a.Mo[(int64_t)t * a.npix + p] : -1;
-      const float* gn = a.gates + ((int64_t)t * a.N + n) * cp;
-      const float* go =
-          t ? a.gates + ((int64_t)(t - 1) * a.N + n) * cp : g_first;
-      const int64_t j = p * a.nf + t;
-      float rm = 0.f;
 #pragma unroll
-      for (int k = 0; k < IT; ++k) {
-        const int v = lane + k * TPS;
-        if (v >= V) break;
-        float pn[8], g1[8], g0[8], d[8];
-        if (r >= 0) {
-          load8f(a.Pt + (int64_t)r * cp + v * 8, pn);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) pn[e] = pv[k][e];
-        }
-        load8f(gn + v * 8, g1);
-        load8f(go + v * 8, g0);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          d[e] = act_f(pn[e], a.act) * g1[e] - act_f(pv[k][e], a.act) * g0[e];
-          pv[k][e] = pn[e];
-        }
-        rm = fmaxf(rm, Vec8<T>::store(dout + j * cp + v * 8, d));
-      }
-#pragma unroll
-      for (int o = 1; o < TPS; o <<= 1) rm = fmaxf(rm, __shfl_xor(rm, o, 64));
-      if (lane == 0) {
-        a.rowmax[j] = __float_as_uint(rm);
-        a.rowpix[j] = (int)((int64_t)t * a.npix + p);
-        a.map[(int64_t)t * a.npix + p] = (int)j;
-      }
+    for (int o = 1; o < TPS; o <<= 1) rm = fmaxf(rm, __shfl_xor(rm, o, 64));
+    if (lane == 0) {
+      a.rowmax[j] = __float_as_uint(rm);
+      a.rowpix[j] = (int)((int64_t)t * a.npix + p);
+      a.map[(int64_t)t * a.npix + p] = (int)j;
     }
   }
+  if (last >= 0) {
+#pragma unroll
+    for (int k = 0; k < IT; ++k) {
+      const int v = lane + k * TPS;
+      if (v >= V) break;
+      float pl[8];
+      load8f(a.Pt + (int64_t)last * cp + v * 8, pl);
+      state_store8(a.P, a.p16, p * cp + v * 8, pl);
+    }
+    if (lane == 0) a.aff[p] = 0u;
+  }
+}
+
+template <typename T, int TPS>
+__global__ __launch_bounds__(256) void k_chunk_se_emit(ChunkSeArgs a) {
+  constexpr int R = 256 / TPS;
+  const int64_t p = (int64_t)blockIdx.x * R + threadIdx.x / TPS;
+  if (p < a.npix)
+    with_act(a.act, [&](auto act_tag) {
+      chunk_se_emit_site<T, TPS, decltype(act_tag)::value>(
+          a, p, threadIdx.x % TPS);
+    });
   if (blockIdx.x == 0 && threadIdx.x == 0)
     *a.cnt_rows = (u64)(a.npix * a.nf);
 }
