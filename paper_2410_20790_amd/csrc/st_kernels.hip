@@ -3415,6 +3415,58 @@ __global__ __launch_bounds__(256) void k_chunk_scan_prep_rgb8(
   }
 }
 
+// The same decisions for pixels of NV whole 16-byte vectors (aligned frames):
+// vector loads, and the pixel at hand in registers (a channel loop of unknown
+// length kept it in scratch: 13.7 us for three 64x64 frames of 16 f32
+// channels, now 3.8 us).
+template <typename T, int NV>
+__global__ __launch_bounds__(256) void k_chunk_scan_prep_vec(
+    ChunkScanArgs a) {
+  constexpr int VEC = 16 / (int)sizeof(T);
+  const uint4* x = (const uint4*)a.x;
+  const uint4* xhat = (const uint4*)a.xhat;
+  const float thr = a.thr_dev ? *a.thr_dev : a.thr;
+  for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < a.npix;
+       p += (int64_t)gridDim.x * 256) {
+    uint4 xh[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) xh[v] = xhat[p * NV + v];
+    uint8_t cur = 0xFF;
+    for (int t = 0; t < a.nf; ++t) {
+      const int64_t i = (int64_t)t * a.npix + p;
+      uint4 xt[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) xt[v] = x[i * NV + v];
+      float m = 0.f;
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+          m = fmaxf(m, fabsf(to_f(((const T*)&xt[v])[e]) -
+                             to_f(((const T*)&xh[v])[e])));
+      const bool k = m > thr;
+      a.keep[p * a.nf + t] = k ? 1 : 0;
+      a.base[i] = cur;
+      if (k) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) xh[v] = xt[v];
+        cur = (uint8_t)t;
+      }
+    }
+    a.last[p] = cur;
+  }
+}
+
+// 16-byte vectors of a pixel of C channels if its rows and frames hold whole
+// aligned vectors (1, 2 or 4 of them), else 0.
+template <typename T>
+static int pixel_vectors(int C, int Cp, const void* x, const void* xhat) {
+  const int bytes = C * (int)sizeof(T);
+  const bool ok = C == Cp && (bytes == 16 || bytes == 32 || bytes == 64) &&
+                  (((uintptr_t)x | (uintptr_t)xhat) & 15) == 0;
+  return ok ? bytes / 16 : 0;
+}
+
 template <typename T>
 struct ChunkScanPred {
   const T* x;
@@ -3426,6 +3478,7 @@ struct ChunkScanPred {
   int* act;
   int* map;
   int C, Cp, nf;
+  int nv;  // 16-byte vectors per pixel, or 0 (pixel_vectors)
   int64_t npix;
   ConsList cons;
   struct Item {
@@ -3443,8 +3496,20 @@ struct ChunkScanPred {
     const T* xt = x + i * C;
     const T* xb = b == 0xFF ? xhat + p * C : x + ((int64_t)b * npix + p) * C;
     T* r = rows + (int64_t)pos * Cp;
-    for (int c = 0; c < Cp; ++c)
-      r[c] = c < C ? from_f<T>(to_f(xt[c]) - to_f(xb[c])) : zero_v<T>();
+    if (nv) {
+      for (int v = 0; v < nv; ++v) {
+        const uint4 n4 = ((const uint4*)xt)[v], o4 = ((const uint4*)xb)[v];
+        uint4 d4;
+#pragma unroll
+        for (int e = 0; e < 16 / (int)sizeof(T); ++e)
+          ((T*)&d4)[e] = from_f<T>(to_f(((const T*)&n4)[e]) -
+                                   to_f(((const T*)&o4)[e]));
+        ((uint4*)r)[v] = d4;
+      }
+    } else {
+      for (int c = 0; c < Cp; ++c)
+        r[c] = c < C ? from_f<T>(to_f(xt[c]) - to_f(xb[c])) : zero_v<T>();
+    }
     rowpix[pos] = (int)i;
     act[pos] = (int)i;
     map[i] = (int)pos;
@@ -3458,14 +3523,18 @@ struct ChunkScanPred {
 };
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_chunk_xhat_commit(ChunkScanArgs a) {
+__global__ __launch_bounds__(256) void k_chunk_xhat_commit(ChunkScanArgs a,
+                                                           int nv) {
   const T* x = (const T*)a.x;
   T* xhat = (T*)a.xhat;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < a.npix;
        p += (int64_t)gridDim.x * 256) {
     const uint8_t b = a.last[p];
     if (b == 0xFF) continue;
-    for (int c = 0; c < a.C; ++c)
+    for (int v = 0; v < nv; ++v)
+      ((uint4*)xhat)[p * nv + v] =
+          ((const uint4*)x)[((int64_t)b * a.npix + p) * nv + v];
+    for (int c = 0; !nv && c < a.C; ++c)
       xhat[p * a.C + c] = x[((int64_t)b * a.npix + p) * a.C + c];
   }
 }
@@ -3484,18 +3553,26 @@ static void chunk_scan_t(const Prof& pf, hipStream_t s,
       k_chunk_scan_prep_rgb8<T>
           <<<grid_for(a.npix / 8, 4096), 256, 0, s>>>(a);
   }
-  if (!rgb8)
-    k_chunk_scan_prep<T><<<grid_for(a.npix, 4096), 256, 0, s>>>(a);
+  const int nv = pixel_vectors<T>(a.C, a.Cp, a.x, a.xhat);
+  const int grid = grid_for(a.npix, 4096);
+  if (nv == 1)
+    k_chunk_scan_prep_vec<T, 1><<<grid, 256, 0, s>>>(a);
+  else if (nv == 2)
+    k_chunk_scan_prep_vec<T, 2><<<grid, 256, 0, s>>>(a);
+  else if (nv == 4)
+    k_chunk_scan_prep_vec<T, 4><<<grid, 256, 0, s>>>(a);
+  else if (!rgb8)
+    k_chunk_scan_prep<T><<<grid, 256, 0, s>>>(a);
   prof_end(pf, 0, s);
   ChunkScanPred<T> p{(const T*)a.x, (const T*)a.xhat, a.keep, a.base,
                      (T*)a.rows, a.rowpix, a.act, a.map, a.C, a.Cp, a.nf,
-                     a.npix, a.cons};
+                     nv, a.npix, a.cons};
   const int64_t items = (int64_t)a.nf * a.npix;
   run_compact(pf, 1 /*ST_K_SCAN_COMPACT*/, s, nullptr, items, items, a.tiles,
               a.tiles_clear,
               a.cnt_rows, a.cnt_act, p);
   prof_begin(pf, 1 /*ST_K_SCAN_COMPACT*/, s);
-  k_chunk_xhat_commit<T><<<grid_for(a.npix, 4096), 256, 0, s>>>(a);
+  k_chunk_xhat_commit<T><<<grid_for(a.npix, 4096), 256, 0, s>>>(a, nv);
   prof_end(pf, 1, s);
 }
 
@@ -4033,7 +4110,16 @@ void launch_cleanup(const Prof& pf, hipStream_t s, const CleanEntry* tab,
 template <typename T>
 __global__ __launch_bounds__(256) void k_dense_input(const T* x, T* xhat,
                                                      T* rows, int C, int Cp,
-                                                     int64_t npix) {
+                                                     int64_t npix, int nv) {
+  // whole-vector pixels are copied as vectors
+  const int64_t nvec = npix * nv;
+  for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < nvec;
+       v += (int64_t)gridDim.x * 256) {
+    const uint4 w = ((const uint4*)x)[v];
+    ((uint4*)xhat)[v] = w;
+    ((uint4*)rows)[v] = w;
+  }
+  if (nv) return;
   for (int64_t p = (int64_t)blockIdx.x * 256 + threadIdx.x; p < npix;
        p += (int64_t)gridDim.x * 256) {
     for (int c = 0; c < Cp; ++c) {
@@ -4050,17 +4136,20 @@ __global__ __launch_bounds__(256) void k_dense_input(const T* x, T* xhat,
 void launch_dense_input(const Prof& pf, hipStream_t s, int dtype,
                         const void* x, void* xhat, void* rows, int C, int Cp,
                         int64_t npix) {
-  const int grid = grid_for(npix, 8192);
+  const int nv = dtype == 0 ? pixel_vectors<float>(C, Cp, x, xhat)
+                            : pixel_vectors<_Float16>(C, Cp, x, xhat);
+  const int grid = grid_for(npix * (nv ? nv : 1), 8192);
   prof_begin(pf, 1 /*ST_K_SCAN_COMPACT*/, s);
   if (dtype == 0)
     k_dense_input<float><<<grid, 256, 0, s>>>(
-        (const float*)x, (float*)xhat, (float*)rows, C, Cp, npix);
+        (const float*)x, (float*)xhat, (float*)rows, C, Cp, npix, nv);
   else if (dtype == 1)
     k_dense_input<_Float16><<<grid, 256, 0, s>>>(
-        (const _Float16*)x, (_Float16*)xhat, (_Float16*)rows, C, Cp, npix);
+        (const _Float16*)x, (_Float16*)xhat, (_Float16*)rows, C, Cp, npix,
+        nv);
   else
     k_dense_input<bf16_t><<<grid, 256, 0, s>>>(
-        (const bf16_t*)x, (bf16_t*)xhat, (bf16_t*)rows, C, Cp, npix);
+        (const bf16_t*)x, (bf16_t*)xhat, (bf16_t*)rows, C, Cp, npix, nv);
   prof_end(pf, 1, s);
 }
 
