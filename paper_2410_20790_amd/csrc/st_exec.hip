@@ -472,7 +472,7 @@ static st_status encode_reference(st_net* net, const void* frame, float* out,
     a.split_max = L.split_max;
     a.dense = 1;
     a.g = conv_geo(L);
-    if (L.dw && dense_dw_takes(a))
+    if (L.dw && net->N <= 65535 && dense_dw_takes(a))  // (an image per grid row)
       launch_dense_dw(pfl, s, net->dtype, a, net->N);
     else if (L.dw)
       launch_conv_dw(pfl, s, net->dtype, a);

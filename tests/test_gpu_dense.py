@@ -113,7 +113,8 @@ def test_dense_residual(dtype, hw):
 
 # (dtype, batch, H, W, C, k, s, se_mid): channels below, at and past the
 # vectors a block's threads share (65 of them: a ragged second block row),
-# widths around a strip's four pixels, one pixel, both windows and strides
+# widths around a strip's four pixels, one pixel, both windows and strides,
+# more images than a launch has grid rows
 DW_CASES = [
     ("bf16", 1, 1, 1, 8, 3, 1, 0),
     ("f16", 2, 5, 3, 24, 5, 1, 3),
@@ -123,6 +124,7 @@ DW_CASES = [
     ("f32", 2, 7, 9, 1152, 5, 1, 48),
     ("bf16", 1, 70, 131, 32, 3, 1, 8),
     ("f32", 1, 11, 12, 16, 5, 2, 0),
+    ("bf16", 65536, 1, 2, 8, 3, 1, 0),
 ]
 
 
