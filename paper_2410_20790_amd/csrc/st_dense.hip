@@ -149,13 +149,18 @@ struct DenseLoader {
   }
 };
 
+// How a tile's reduction is summed: in one chain; in `parts` partial sums
+// that the block adds in order; or block row y reduces part y of the stages
+// and writes f32 partial rows part[y][pixel][channel], which the split
+// epilogue adds in order and finishes.
+enum { kSumChain = 0, kSumParts = 1, kSumSplit = 2 };
+
 // Tile of BM pixels by BN channels in waves of WM by WN, S stages in LDS.
-// SPLIT: block row y reduces its part of the stages and writes f32 partial
-// rows part[y][pixel][channel], which the split epilogue sums and finishes.
 template <typename T, int KIND, int BM, int BN, int WM, int WN, int S,
-          bool SPLIT>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_dense_conv(ConvArgs a, int tiles_n,
-                                                    int tiles, int chunk) {
+          int SUM>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
+void k_dense_conv(ConvArgs a, int tiles_n, int tiles, int chunk, int parts) {
+  constexpr bool SPLIT = SUM == kSumSplit;
   constexpr int WAVES_N = BN / WN, NW = BM / WM * WAVES_N;
   constexpr int PQ = BM / 8 / NW, WQ = BN / 8 / NW, L = PQ + WQ;
   constexpr int IM = WM / 16, JN = WN / 16;
@@ -221,19 +226,53 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_dense_conv(ConvA
   if constexpr (S > 3) ld.template issue<BM>(a, s2);
   constexpr int AH = (S - 2) * L;
   const int pr = wm * WM, wr = BM + wn * WN;
+  v4f sum[SUM == kSumParts ? IM : 1][SUM == kSumParts ? JN : 1];
+  int part_end = nst, part = 0;
+  if constexpr (SUM == kSumParts) {
+    part_end = nst / parts;
+#pragma unroll
+    for (int i = 0; i < IM; ++i)
+#pragma unroll
+      for (int j = 0; j < JN; ++j) sum[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+  }
+  // the stage before `next` is done: the last of a part?
+  auto part_done = [&](int next) {
+    if constexpr (SUM == kSumParts) {
+      if (next != part_end) return;
+      ++part;
+      part_end = (part + 1) * nst / parts;
+#pragma unroll
+      for (int i = 0; i < IM; ++i)
+#pragma unroll
+        for (int j = 0; j < JN; ++j) {
+          sum[i][j] += acc[i][j];
+          acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
+    }
+  };
   for (int st = st0; st < st1; st += S) {
     char* const last = S == 2 ? s1 : S == 3 ? s2 : s3;
     stage_turn<T, BM, AH>(a, ld, s0, last, pr, wr, l16, lg, acc);
+    part_done(st + 1);
     if (st + 1 >= st1) break;
     stage_turn<T, BM, AH>(a, ld, s1, s0, pr, wr, l16, lg, acc);
+    part_done(st + 2);
     if constexpr (S > 2) {
       if (st + 2 >= st1) break;
       stage_turn<T, BM, AH>(a, ld, s2, s1, pr, wr, l16, lg, acc);
+      part_done(st + 3);
     }
     if constexpr (S > 3) {
       if (st + 3 >= st1) break;
       stage_turn<T, BM, AH>(a, ld, s3, s2, pr, wr, l16, lg, acc);
+      part_done(st + 4);
     }
+  }
+  if constexpr (SUM == kSumParts) {  // (the last part's end is nst)
+#pragma unroll
+    for (int i = 0; i < IM; ++i)
+#pragma unroll
+      for (int j = 0; j < JN; ++j) acc[i][j] = sum[i][j];
   }
 
   if constexpr (SPLIT) {
@@ -292,24 +331,23 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64) void k_dense_conv(ConvA
   });
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int S,
-          bool SPLIT = false>
-void dense_launch(hipStream_t s, const ConvArgs& a, int splits = 1) {
+template <typename T, int BM, int BN, int WM, int WN, int S, int SUM>
+void dense_launch(hipStream_t s, const ConvArgs& a, int parts) {
   constexpr int KC = kRowBytes / (int)sizeof(T);
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   const int tiles_n = (a.cout_p + BN - 1) / BN;
   const int tiles = (int)((a.capO + BM - 1) / BM) * tiles_n;
   const int chunk = (tiles + kDenseXcd - 1) / kDenseXcd;
-  const dim3 grid(chunk * kDenseXcd, splits);
+  const dim3 grid(chunk * kDenseXcd, SUM == kSumSplit ? parts : 1);
   if (a.K == 1)
-    k_dense_conv<T, kSrcPoint, BM, BN, WM, WN, S, SPLIT>
-        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk);
+    k_dense_conv<T, kSrcPoint, BM, BN, WM, WN, S, SUM>
+        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk, parts);
   else if (a.cin_p % KC == 0)
-    k_dense_conv<T, kSrcAligned, BM, BN, WM, WN, S, SPLIT>
-        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk);
+    k_dense_conv<T, kSrcAligned, BM, BN, WM, WN, S, SUM>
+        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk, parts);
   else
-    k_dense_conv<T, kSrcAny, BM, BN, WM, WN, S, SPLIT>
-        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk);
+    k_dense_conv<T, kSrcAny, BM, BN, WM, WN, S, SUM>
+        <<<grid, NT, 0, s>>>(a, tiles_n, tiles, chunk, parts);
 }
 
 // Tile shape by the tiles a launch has for the chip's 256 CUs (measured on
@@ -324,45 +362,47 @@ void dense_launch(hipStream_t s, const ConvArgs& a, int splits = 1) {
 //  - 64x64 with 4 stages else (3x3 512 on 2048 pixels: 28 against 35), and
 //    128x32 for at most 32 channels, where half of a 64-channel tile would
 //    be padding.
-// With fewer than 128 tiles of 64x64 a long reduction is split, enough for
-// about 256 blocks, at least 8 stages each (f32, whose products bound it and
-// whose sums the shorter chains keep closer: under 1024 tiles, enough for
-// 1024 blocks, at least 4 stages).
+template <typename T, int SUM>
+void dense_tiles(hipStream_t s, const ConvArgs& a, int parts) {
+  const int64_t m128 = (a.capO + 127) / 128;
+  const int64_t n64 = (a.cout_p + 63) / 64, n128 = (a.cout_p + 127) / 128;
+  if (a.cout_p <= 32 && m128 >= 224)
+    dense_launch<T, 128, 32, 32, 32, 3, SUM>(s, a, parts);
+  else if (a.cout_p > 64 && m128 * n128 >= 224)
+    dense_launch<T, 128, 128, 64, 32, 3, SUM>(s, a, parts);
+  else if (SUM == kSumChain && m128 * n64 >= 1024)  // (parts: 1023 of 64x64)
+    dense_launch<T, 128, 64, 32, 32, 2, kSumChain>(s, a, 1);
+  else if (m128 * n64 >= 224)
+    dense_launch<T, 128, 64, 32, 32, 3, SUM>(s, a, parts);
+  else
+    dense_launch<T, 64, 64, 32, 32, 4, SUM>(s, a, parts);
+}
+
+// A long reduction is summed in parts.  Half precision: the parts of the
+// diff frames' split (split_count of the 64x64 tiles, whatever tile the rule
+// above takes), so that a state is the same sum in the same order whichever
+// kernel computes it; with fewer than 128 tiles of 64x64 every part has its
+// own block, with more the block adds its parts itself.  f32 (whose products
+// bound it, whose stages are shorter and whose columns are added in another
+// order anyway): blocks of their own, where the rule above would take 64x64.
 template <typename T>
 int dense_conv(hipStream_t s, const ConvArgs& a) {
   constexpr int KC = kRowBytes / (int)sizeof(T);
-  const int64_t m128 = (a.capO + 127) / 128, m64 = (a.capO + 63) / 64;
-  const int64_t n64 = (a.cout_p + 63) / 64, n128 = (a.cout_p + 127) / 128;
+  const int64_t tiles = ((a.capO + 63) / 64) * ((a.cout_p + 63) / 64);
   const int nst = (a.K * a.cin_p + KC - 1) / KC;
-  if (a.cout_p <= 32 && m128 >= 224) {
-    dense_launch<T, 128, 32, 32, 32, 3>(s, a);
-    return 1;
+  const int parts = split_count(tiles, nst, a.split_max);
+  const int64_t t128 = ((a.capO + 127) / 128) * ((a.cout_p + 63) / 64);
+  if (parts > 1 && (sizeof(T) == 4 ? t128 < 224 : tiles < 128)) {
+    dense_launch<T, 64, 64, 32, 32, 4, kSumSplit>(s, a, parts);
+    return parts;
   }
-  if (a.cout_p > 64 && m128 * n128 >= 224) {
-    dense_launch<T, 128, 128, 64, 32, 3>(s, a);
-    return 1;
+  if constexpr (sizeof(T) == 2) {
+    if (parts > 1) {
+      dense_tiles<T, kSumParts>(s, a, parts);
+      return 1;
+    }
   }
-  if (m128 * n64 >= 1024) {
-    dense_launch<T, 128, 64, 32, 32, 2>(s, a);
-    return 1;
-  }
-  if (m128 * n64 >= 224) {
-    dense_launch<T, 128, 64, 32, 32, 3>(s, a);
-    return 1;
-  }
-  int splits = 1;
-  constexpr int kBlocks = sizeof(T) == 4 ? 1024 : 256;
-  constexpr int kStages = sizeof(T) == 4 ? 4 : 8;
-  if (a.split_max > 1 && m64 * n64 < (sizeof(T) == 4 ? 1024 : 128)) {
-    splits = (int)((kBlocks + m64 * n64 - 1) / (m64 * n64));
-    splits = splits < a.split_max ? splits : a.split_max;
-    splits = splits < nst / kStages ? splits : nst / kStages;
-  }
-  if (splits > 1) {
-    dense_launch<T, 64, 64, 32, 32, 4, true>(s, a, splits);
-    return splits;
-  }
-  dense_launch<T, 64, 64, 32, 32, 4>(s, a);
+  dense_tiles<T, kSumChain>(s, a, 1);
   return 1;
 }
 

@@ -44,14 +44,16 @@ __device__ __forceinline__ float store4(T* p, const float* f) {
 // Splits of the reduction per output tile for this frame: enough work units
 // (tiles x splits) to give every CU several, at most split_max, and at
 // least kSplitMinStages stages per split.  The GEMM and its split epilogue
-// both derive it from the same device count.
+// both derive it from the same device count; the dense pass sums in as many
+// parts (st_dense.hip).
 constexpr int kSplitTarget = 1024, kSplitMinStages = 4;
-__device__ __forceinline__ int split_count(int64_t ntiles, int nst, int smax) {
+__host__ __device__ __forceinline__ int split_count(int64_t ntiles, int nst,
+                                                    int smax) {
   if (smax <= 1 || ntiles <= 0) return 1;
   int64_t sp = (kSplitTarget + ntiles - 1) / ntiles;
-  sp = min(sp, (int64_t)smax);
-  sp = min(sp, (int64_t)max(1, nst / kSplitMinStages));
-  return (int)max(sp, (int64_t)1);
+  if (sp > smax) sp = smax;
+  if (sp > nst / kSplitMinStages) sp = nst / kSplitMinStages;
+  return sp > 1 ? (int)sp : 1;
 }
 
 // Reduction stages of a layer that hold real (not padding) columns, for

@@ -75,6 +75,56 @@ def test_dense_convolution(case, act):
     assert bool((err <= bound).all()), float((err / bound).max())
 
 
+# (H, W, c_in, c_out, k, parts): parts by blocks of their own (1 and 96 tiles
+# of 64x64), then by the block itself for every tile shape (64x64, 128x64,
+# 128x128, 128x32), ragged in pixels
+ORDER_CASES = [
+    (7, 9, 2048, 40, 1, 4),
+    (62, 99, 2048, 64, 1, 4),
+    (64, 128, 2048, 56, 1, 4),
+    (43, 190, 256, 64, 3, 4),
+    (79, 121, 2048, 256, 1, 2),
+    (85, 85, 256, 512, 3, 2),
+    (129, 254, 2048, 32, 1, 2),
+]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("case", ORDER_CASES,
+                         ids=lambda c: "-".join(map(str, c)))
+def test_dense_sum_order(case, dtype):
+    """A long half-precision reduction is the sum, in order, of its parts'
+    sums (as the split of a diff frame adds them).  A stage (64 columns of
+    the reduction) has one product: 2^28 in the first, -2^28 in the last, 8
+    in some between, which 2^28 swallows and a part without it keeps (as
+    multiples of 32, so that no sum is a tie of its rounding)."""
+    from paper_2410_20790_amd import SparseTemNet
+    h, w, cin, cout, k, parts = case
+    print("order", case, dtype, flush=True)
+    nst, spk = cin * k * k // 64, cin // 64
+    vals = np.zeros(nst, np.float32)
+    for j in range(1, parts):
+        at = j * nst // parts
+        vals[at:at + (4 if j == parts - 1 else 8)] = 8
+    vals[0], vals[-1] = 2.0 ** 28, -2.0 ** 28
+    L = LayerSpec(src=-1, c_in=cin, c_out=cout, k=(k, k), s=(1, 1),
+                  p=(k // 2, k // 2), act=0)
+    L.weight = np.zeros((cout, cin, k, k), np.float32)
+    for st, v in enumerate(vals):
+        o = st // spk
+        L.weight[:, st % spk * 64, o // k, o % k] = v / 2 ** 13
+    net = SparseTemNet([L], 1, h, w, cin, dtype)
+    try:
+        x = torch.full((1, h, w, cin), 2.0 ** 13, dtype=net.tdtype,
+                       device="cuda")
+        out = net.encode_reference(x).cpu().numpy()
+    finally:
+        net.close()
+    want = vals[1:-1].sum()  # (one chain would give 0)
+    m = k // 2  # the pixels whose windows lie inside
+    assert (out[0, m:h - m, m:w - m] == want).all(), (out[0, m, m, 0], want)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("hw", [(9, 7), (169, 170)])
 def test_dense_residual(dtype, hw):
