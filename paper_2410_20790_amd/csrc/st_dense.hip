@@ -378,31 +378,28 @@ void dense_tiles(hipStream_t s, const ConvArgs& a, int parts) {
     dense_launch<T, 64, 64, 32, 32, 4, SUM>(s, a, parts);
 }
 
-// A long reduction is summed in parts.  Half precision: the parts of the
-// diff frames' split (split_count of the 64x64 tiles, whatever tile the rule
-// above takes), so that a state is the same sum in the same order whichever
-// kernel computes it; with fewer than 128 tiles of 64x64 every part has its
-// own block, with more the block adds its parts itself.  f32 (whose products
-// bound it, whose stages are shorter and whose columns are added in another
-// order anyway): blocks of their own, where the rule above would take 64x64.
+// A long reduction is summed in parts, as many as the diff frames' split
+// (split_count of the 64x64 tiles, whatever tile the rule above takes), so
+// that no chain of sums is longer and, in half precision, a state is the same
+// sum in the same order whichever kernel computes it (f32 columns are added
+// in another order).  With few tiles every part has a block of its own (half
+// precision: fewer than 128; f32, whose products bound it: where the rule
+// above would take 64x64), with more the block adds its parts itself.
 template <typename T>
 int dense_conv(hipStream_t s, const ConvArgs& a) {
   constexpr int KC = kRowBytes / (int)sizeof(T);
   const int64_t tiles = ((a.capO + 63) / 64) * ((a.cout_p + 63) / 64);
+  const int64_t t128 = ((a.capO + 127) / 128) * ((a.cout_p + 63) / 64);
   const int nst = (a.K * a.cin_p + KC - 1) / KC;
   const int parts = split_count(tiles, nst, a.split_max);
-  const int64_t t128 = ((a.capO + 127) / 128) * ((a.cout_p + 63) / 64);
   if (parts > 1 && (sizeof(T) == 4 ? t128 < 224 : tiles < 128)) {
     dense_launch<T, 64, 64, 32, 32, 4, kSumSplit>(s, a, parts);
     return parts;
   }
-  if constexpr (sizeof(T) == 2) {
-    if (parts > 1) {
-      dense_tiles<T, kSumParts>(s, a, parts);
-      return 1;
-    }
-  }
-  dense_tiles<T, kSumChain>(s, a, 1);
+  if (parts > 1)
+    dense_tiles<T, kSumParts>(s, a, parts);
+  else
+    dense_tiles<T, kSumChain>(s, a, 1);
   return 1;
 }
 

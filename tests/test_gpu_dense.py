@@ -76,8 +76,9 @@ def test_dense_convolution(case, act):
 
 
 # (H, W, c_in, c_out, k, parts): parts by blocks of their own (1 and 96 tiles
-# of 64x64), then by the block itself for every tile shape (64x64, 128x64,
-# 128x128, 128x32), ragged in pixels
+# of 64x64; f32: every case of 4 parts, which then are 8), then by the block
+# itself for every tile shape (64x64, 128x64, 128x128, 128x32), ragged in
+# pixels
 ORDER_CASES = [
     (7, 9, 2048, 40, 1, 4),
     (62, 99, 2048, 64, 1, 4),
@@ -89,19 +90,22 @@ ORDER_CASES = [
 ]
 
 
-@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("case", ORDER_CASES,
                          ids=lambda c: "-".join(map(str, c)))
 def test_dense_sum_order(case, dtype):
-    """A long half-precision reduction is the sum, in order, of its parts'
-    sums (as the split of a diff frame adds them).  A stage (64 columns of
-    the reduction) has one product: 2^28 in the first, -2^28 in the last, 8
+    """A long reduction is the sum, in order, of its parts' sums (as the
+    split of a diff frame adds them).  A stage (128 bytes of the reduction's
+    columns) has one product: 2^28 in the first, -2^28 in the last, 8
     in some between, which 2^28 swallows and a part without it keeps (as
     multiples of 32, so that no sum is a tie of its rounding)."""
     from paper_2410_20790_amd import SparseTemNet
     h, w, cin, cout, k, parts = case
     print("order", case, dtype, flush=True)
-    nst, spk = cin * k * k // 64, cin // 64
+    kc = 32 if dtype == "f32" else 64
+    nst, spk = cin * k * k // kc, cin // kc
+    if dtype == "f32" and parts == 4:
+        parts = 8
     vals = np.zeros(nst, np.float32)
     for j in range(1, parts):
         at = j * nst // parts
@@ -112,7 +116,7 @@ def test_dense_sum_order(case, dtype):
     L.weight = np.zeros((cout, cin, k, k), np.float32)
     for st, v in enumerate(vals):
         o = st // spk
-        L.weight[:, st % spk * 64, o // k, o % k] = v / 2 ** 13
+        L.weight[:, st % spk * kc, o // k, o % k] = v / 2 ** 13
     net = SparseTemNet([L], 1, h, w, cin, dtype)
     try:
         x = torch.full((1, h, w, cin), 2.0 ** 13, dtype=net.tdtype,
