@@ -235,8 +235,18 @@ __attribute__((amdgpu_waves_per_eu(WPE))) void k_gather_conv(ConvArgs a) {
     if constexpr (!POINT)
       kmask = __ballot(lane < K && s_act[lane < K ? lane : 0]);
     const int nact = POINT ? spk : (int)__popcll(kmask) * spk;
-    const int lo = SPLIT ? sp * nact / sp_n : 0;
-    const int nst = SPLIT ? (sp + 1) * nact / sp_n - lo : nact;
+    // A split's share of the active stages.  Half precision: those of its
+    // share of the whole reduction, so that a row's sum does not depend on
+    // which rows share its tile; f32: an equal share (CRNN-VGG chunks of 16:
+    // 625 us a group against 638).
+    auto cut = [&](int j) {
+      if (POINT || sizeof(T) == 4) return j * nact / sp_n;
+      const int r = j * (K * spk) / sp_n, k = r / spk;
+      return (int)__popcll(kmask & ((1ull << k) - 1)) * spk +
+             ((kmask >> k) & 1ull ? r - k * spk : 0);
+    };
+    const int lo = SPLIT ? cut(sp) : 0;
+    const int nst = (SPLIT ? cut(sp + 1) : nact) - lo;
 
     // what the epilogue reads, requested before the first stage
     const int c = n0 + wn * 32 + lg * 8;  // this lane's eight channels

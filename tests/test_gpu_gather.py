@@ -71,3 +71,31 @@ def test_gather(case, dtype):
     finally:
         for g in nets:
             g.close()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_gather_split_order(dtype):
+    """A half-precision split is cut from the whole window's stages (64
+    columns each), also where a tile's rows (one image row) reach only some
+    of its offsets: 3x3 over 256 channels in four parts of nine stages, of
+    which the middle row's offsets have stages 12 to 23.  2^28 in stage 12
+    swallows the 8s in its part, up to 17."""
+    from paper_2410_20790_amd import SparseTemNet
+    print("split order", dtype, flush=True)
+    W = 40
+    vals = np.zeros(36, np.float32)
+    vals[15:18] = vals[18:21] = 8, 8, 16
+    vals[12], vals[23] = 2.0 ** 28, -2.0 ** 28
+    L = LayerSpec(src=-1, c_in=256, c_out=64, k=(3, 3), p=(1, 1), act=0)
+    L.weight = np.zeros((64, 256, 3, 3), np.float32)
+    for st, v in enumerate(vals):
+        L.weight[:, st % 4 * 64, st // 4 // 3, st // 4 % 3] = v / 2 ** 13
+    net = SparseTemNet([L], 1, 1, W, 256, dtype)
+    try:
+        x = torch.zeros((1, 1, W, 256), dtype=net.tdtype, device="cuda")
+        net.encode_reference(x)
+        out = net.encode_diff(torch.full_like(x, 2.0 ** 13), [0.0, 0.0])
+        out = out.cpu().numpy()
+    finally:
+        net.close()
+    assert (out[0, 0, 1:W - 1] == 32).all(), out[0, 0, :, 0]
