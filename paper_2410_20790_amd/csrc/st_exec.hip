@@ -471,6 +471,7 @@ static st_status encode_reference(st_net* net, const void* frame, float* out,
     a.part = ws.at<float>(net->off_part);
     a.split_max = L.split_max;
     a.dense = 1;
+    a.offset_order = net->carry || net->has_se;
     a.g = conv_geo(L);
     if (L.dw && net->N <= 65535 && dense_dw_takes(a))  // (an image per grid row)
       launch_dense_dw(pfl, s, net->dtype, a, net->N);

@@ -214,6 +214,10 @@ struct ConvArgs {
   // maximum is kept (rowmax NULL)
   int dense;
   Geo g;
+  // dense pass of a net with residual carry or squeeze-excitation: the stem
+  // sums offset by offset, as its diff frames do (k_conv_gemm), not window
+  // row by window row (k_stem_dense)
+  int offset_order;
   int dense_splits;  // splits of the dense pass's partial rows (0: not split)
   // residual carry, dense pass: the view [grid][cout_p] that starts as the
   // emitted rows, or NULL

@@ -2132,8 +2132,10 @@ void k_stem_dense(ConvArgs a) {
 
 // The dense reference pass's stem takes k_stem_dense: half precision, 7x7
 // stride 2 over rows of 4 (padded) channels, at most 64 output channels.
+// (Not with residual carry or squeeze-excitation, whose stems are summed in
+// the order of their diff frames.)
 static bool stem_dense(int dtype, const ConvArgs& a) {
-  return dtype != 0 && a.dense && a.K == 49 && a.cin_p == 4 &&
+  return dtype != 0 && a.dense && !a.offset_order && a.K == 49 && a.cin_p == 4 &&
          a.cout_p <= 64 && a.g.kh == 7 && a.g.kw == 7 && a.g.sh == 2 &&
          a.g.sw == 2 && a.split_max <= 1 && a.g.Wo > 0;
 }

@@ -129,6 +129,43 @@ def test_dense_sum_order(case, dtype):
     assert (out[0, m:h - m, m:w - m] == want).all(), (out[0, m, m, 0], want)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("option", ["carry", "se"])
+def test_stem_sum_order(option, dtype):
+    """With residual carry or squeeze-excitation a 7x7/2 stem's states are
+    summed in the order of its diff frames: a reference frame leaves them bit
+    for bit as a diff frame from zeros does."""
+    from paper_2410_20790_amd import SparseTemNet
+    from paper_2410_20790_amd import binding as B
+    print("stem", option, dtype, flush=True)
+    rng = np.random.default_rng(13)
+    layers = [LayerSpec(src=-1, c_in=3, c_out=40, k=(7, 7), s=(2, 2),
+                        p=(3, 3), act=1),
+              LayerSpec(src=0, c_in=40, c_out=8, k=(1, 1), s=(1, 1),
+                        p=(0, 0), act=2, se_mid=4 * (option == "se"))]
+    for L in layers:
+        n = L.c_in * L.k[0] ** 2
+        L.weight = to_storage(rng.normal(0, n ** -0.5,
+                                         (L.c_out, L.c_in) + L.k), dtype)
+        L.bias = to_storage(rng.normal(0, 1, (L.c_out,)), dtype)
+        if L.se_mid:
+            for name, shape in (("se_w1", (4, 8)), ("se_b1", (4,)),
+                                ("se_w2", (8, 4)), ("se_b2", (8,))):
+                setattr(L, name, to_storage(rng.normal(0, 1, shape), dtype))
+    x = to_storage(rng.normal(0, 1, (2, 33, 141, 3)), dtype)
+    net = SparseTemNet(layers, 2, 33, 141, 3, dtype, carry=option == "carry")
+    try:
+        x = torch.from_numpy(x).to("cuda", net.tdtype)
+        net.encode_reference(x)
+        ref = B.st_debug_state(net.handle, 0, (2, 17, 71, 40))
+        net.encode_reference(torch.zeros_like(x))
+        net.encode_diff(x, [0.0] * 3)
+        diff = B.st_debug_state(net.handle, 0, (2, 17, 71, 40))
+    finally:
+        net.close()
+    assert np.array_equal(ref, diff)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("hw", [(9, 7), (169, 170)])
 def test_dense_residual(dtype, hw):
