@@ -246,9 +246,22 @@ void launch_dense_dw(const Prof& pf, hipStream_t s, int dtype,
 // takes: 1x1 kernels and windows of up to nine offsets over channel counts
 // that fill whole stages (64 half-precision or 32 f32 columns), in every
 // mode but a pooled layer's chunk.  An f32 net with a bf16 state keeps the
-// other kernel's order of sums (see dense_conv_takes).
+// other kernel's order of sums (see dense_conv_takes).  Half-precision 1x1
+// layers with a residual row, over whole stages, leave chunks of more than
+// kGatherShortRuns frames to the other kernel, which holds states and residual
+// rows per run, not per row, and four blocks per CU.  ResNet-50 at 1024x2048,
+// diff frames of a chunk, ms, with them here (and long runs walked) against
+// there: 9 frames, 10% of the sites changed 5.66 and 5.64, 40% 12.87 and
+// 12.40, 80% 18.38 and 17.78 (all of them in the other kernel, as before this
+// one: 5.73, 12.61, 18.03); 6 frames 4.20 and 4.24, 8.55 and 8.49, 11.98 and
+// 11.72 (before: 4.33, 8.62, 11.97); 2 frames 2.53 and 2.61, 3.80 and 3.89,
+// 4.89 and 4.92.
+constexpr int kGatherShortRuns = 6;
 inline bool gather_takes(int dtype, const ConvArgs& a) {
   const int kc = dtype == 0 ? 32 : 64;
+  if (dtype != 0 && a.mode == kModeChunkState && a.nf > kGatherShortRuns &&
+      a.mskip && a.K == 1 && a.cin_p % kc == 0)
+    return false;
   return a.mode != kModeChunkPool && !(dtype == 0 && a.p16) &&
          (a.K == 1 ? a.cin_p % 8 == 0 : a.K <= 9 && a.cin_p % kc == 0);
 }

@@ -41,6 +41,14 @@ CASES = [
     (128, 64, 3, 1, 3, 11, 1, 32, 1.0),     # runs of 32: tiles of one run
     (200, 24, 1, 1, 17, 19, 1, 31, 0.9),
     (512, 64, 3, 1, 5, 6, 1, 3, 0.05),      # split; offsets without rows
+    # chunks of the most frames whose runs are never walked and one more,
+    # tiles around the rows per run that are; residual layers of whole and
+    # of ragged stages; a long reduction
+    (64, 72, 3, 1, 13, 9, 1, 6, 1.0),
+    (64, 72, 3, 1, 13, 9, 1, 7, 1.0),
+    (40, 136, 1, 1, 29, 9, 1, 9, 0.6),
+    (64, 64, 3, 1, 23, 7, 1, 12, 0.3),
+    (264, 40, 1, 1, 9, 33, 1, 32, 0.2),
 ]
 
 
