@@ -387,11 +387,9 @@ void dense_tiles(hipStream_t s, const ConvArgs& a, int parts) {
 // above would take 64x64), with more the block adds its parts itself.
 template <typename T>
 int dense_conv(hipStream_t s, const ConvArgs& a) {
-  constexpr int KC = kRowBytes / (int)sizeof(T);
   const int64_t tiles = ((a.capO + 63) / 64) * ((a.cout_p + 63) / 64);
   const int64_t t128 = ((a.capO + 127) / 128) * ((a.cout_p + 63) / 64);
-  const int nst = (a.K * a.cin_p + KC - 1) / KC;
-  const int parts = split_count(tiles, nst, a.split_max);
+  const int parts = split_count(tiles, a.split_max);
   if (parts > 1 && (sizeof(T) == 4 ? t128 < 224 : tiles < 128)) {
     dense_launch<T, 64, 64, 32, 32, 4, kSumSplit>(s, a, parts);
     return parts;

@@ -160,8 +160,7 @@ __attribute__((amdgpu_waves_per_eu(WPE))) void k_gather_conv(ConvArgs a) {
   const int tiles_n = (cout_p + BN - 1) / BN;
   const int64_t ntiles = tiles_m * tiles_n;
   const int spk = (a.cin_p + KC - 1) / KC;  // stages per offset
-  const int sp_n =
-      SPLIT ? split_count(ntiles, gemm_stages_kc<KC>(a), a.split_max) : 1;
+  const int sp_n = SPLIT ? split_count(ntiles, a.split_max) : 1;
   const int64_t nunits = ntiles * sp_n;
   // each XCD a contiguous range of units (neighbouring tiles gather the same
   // rows), its blocks striding through it

@@ -21,18 +21,20 @@ constexpr int kMaxTiles = kCompactMaxTiles;  // compaction tiles per pass
 constexpr int64_t kMaxGrid = (int64_t)kMaxTiles * 8192;  // sites per grid
 constexpr size_t kAlign = 256;      // workspace sub-buffer alignment
 
+// Reduction splits of a convolution: a layer with at least
+// kSplitMinLayerStages reduction stages (64 half-precision or 16 f32 columns)
+// may split each output tile into up to kSplitMax parts of at least
+// kSplitStages stages when a frame has few tiles (split_count, st_stage.h).
+constexpr int kSplitMinLayerStages = 32;
+constexpr int kSplitStages = 8;
+constexpr int kSplitMax = 8;
+
 // Squeeze-excitation row mapping: each site is handled by a power-of-two
 // group of threads (at most one wave), each thread owning 8-channel vectors;
 // a 256-thread block covers 256 / tps sites side by side.  The squeeze
 // splits each image into about kSePartialFloats / cp site ranges (4..256),
 // so that the partial sums one excitation block reduces stay near
 // kSePartialFloats floats.
-// Reduction splits of the gather-GEMM: a layer with at least
-// kSplitMinLayerStages reduction stages may split each output tile into up
-// to stages / 8 (at most kSplitMax) parts when a frame has few tiles.
-constexpr int kSplitMinLayerStages = 32;
-constexpr int kSplitMax = 8;
-
 constexpr int kSeMaxChannels = 2048;
 constexpr int kSePartialFloats = 16384;
 inline int se_threads_per_site(int cp) {

@@ -734,13 +734,6 @@ __device__ __forceinline__ void lds_store16<bf16_t>(bf16_t* dst, uint4 v) {
 
 constexpr int kGemmBM = 64, kGemmBN = 64, kXcd = 8, kCUs = 256;
 
-// Reduction stages of a layer that hold real (not padding) columns.
-template <typename T>
-__device__ __forceinline__ int gemm_stages(const ConvArgs& a) {
-  constexpr int KC = MmaCfg<T>::KC;
-  return min((int)a.ktot_p, (a.K * a.cin_p + KC - 1) / KC * KC) / KC;
-}
-
 // Finishes one thread's share of an output tile -- row eo of the tile,
 // columns n0 + ec + [0, 16) -- from the reduced values v: adds the bias
 // (reference pass) and the residual delta, then either defers the update
@@ -1134,7 +1127,7 @@ void k_conv_gemm(ConvArgs a) {
   const int spk = ALIGNED ? cin_p / KC : 1;
   // work units: (split, tile) pairs, split-major, so that neighbouring
   // tiles of one split (which gather the same input rows) stay together
-  const int S = SPLIT ? split_count(ntiles, nst, a.split_max) : 1;
+  const int S = SPLIT ? split_count(ntiles, a.split_max) : 1;
   const int64_t nunits = ntiles * S;
   // XCD-aware order: blocks are dealt round-robin over the kXcd XCDs
   // (gridDim.x is a multiple of kXcd); the unit range is cut into kXcd
@@ -1559,9 +1552,8 @@ __global__ __launch_bounds__(256) void k_split_epi(ConvArgs a) {
   const int64_t tiles_m = (nO + BM - 1) / BM;
   const int tiles_n = (a.cout_p + BN - 1) / BN;
   const int64_t ntiles = tiles_m * tiles_n;
-  const int S = REF && a.dense_splits
-                    ? a.dense_splits
-                    : split_count(ntiles, gemm_stages<T>(a), a.split_max);
+  const int S = REF && a.dense_splits ? a.dense_splits
+                                      : split_count(ntiles, a.split_max);
   const int tid = threadIdx.x, cout_p = a.cout_p;
   const int em = tid >> 2, ec = (tid & 3) * 16;
   const T* dskip = (const T*)a.dskip;

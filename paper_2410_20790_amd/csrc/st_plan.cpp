@@ -282,7 +282,7 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
     if (!L.dw) {
       const int64_t stages = L.ktot_p / kc;
       if (stages >= kSplitMinLayerStages)
-        L.split_max = (int)std::min<int64_t>(kSplitMax, stages / 8);
+        L.split_max = (int)std::min<int64_t>(kSplitMax, stages / kSplitStages);
       part_bytes = std::max<size_t>(
           part_bytes, L.split_max > 1 ? sizeof(float) * L.split_max *
                                             citems * L.cout_p

@@ -42,18 +42,17 @@ __device__ __forceinline__ float store4(T* p, const float* f) {
 }
 
 // Splits of the reduction per output tile for this frame: enough work units
-// (tiles x splits) to give every CU several, at most split_max, and at
-// least kSplitMinStages stages per split.  The GEMM and its split epilogue
-// both derive it from the same device count; the dense pass sums in as many
-// parts (st_dense.hip).
-constexpr int kSplitTarget = 1024, kSplitMinStages = 4;
-__host__ __device__ __forceinline__ int split_count(int64_t ntiles, int nst,
-                                                    int smax) {
-  if (smax <= 1 || ntiles <= 0) return 1;
-  int64_t sp = (kSplitTarget + ntiles - 1) / ntiles;
-  if (sp > smax) sp = smax;
-  if (sp > nst / kSplitMinStages) sp = nst / kSplitMinStages;
-  return sp > 1 ? (int)sp : 1;
+// (tiles x splits) to give every CU several, at most split_max (which leaves
+// every split at least kSplitStages of the planner's stages).  The kernels
+// that write the partial tiles and the split epilogue that adds them derive
+// it from the same two numbers, whatever the stages of either; the dense pass
+// sums in as many parts (st_dense.hip).
+constexpr int kSplitTarget = 1024;
+__host__ __device__ __forceinline__ int split_count(int64_t ntiles,
+                                                    int split_max) {
+  if (split_max <= 1 || ntiles <= 0) return 1;
+  const int64_t sp = (kSplitTarget + ntiles - 1) / ntiles;
+  return sp < split_max ? (int)sp : split_max;
 }
 
 // Reduction stages of a layer that hold real (not padding) columns, for
