@@ -311,8 +311,10 @@ void k_dense_conv(ConvArgs a, int tiles_n, int tiles, int chunk, int parts) {
         if (a.mode != kModeLinear) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) v[e] = state_round(a.p16, v[e]);
-          if (a.p16) {
-            state_store8(a.P, true, o * cout_p + c, v);
+          if (a.p16 || a.mode == kModeStateOnly) {
+            // (a state without rows is read by the next launch: the pool,
+            // the squeeze or the output)
+            state_store8(a.P, a.p16, o * cout_p + c, v);
           } else {
             // the next reader of the state is another frame: streamed past
             // the caches, which keep the rows the next layer reads
