@@ -203,7 +203,8 @@ st_status st_bind_workspace(st_net* net, void* dev_ptr, uint64_t bytes,
  * share the array must not run at the same time (their work on one device
  * would race); binding again resets the net to "no reference".
  * Errors: ST_ERR_INVALID_ARG (NULL net), ST_ERR_WORKSPACE
- * (st_workspace_bytes() above ST_STATIC_WORKSPACE_BYTES), ST_ERR_HIP. */
+ * (st_workspace_bytes() above ST_STATIC_WORKSPACE_BYTES; with residual carry
+ * or squeeze-excitation a few bytes per layer do not count), ST_ERR_HIP. */
 st_status st_bind_workspace_static(st_net* net, void* stream);
 
 /* Dense pass on a reference frame (paper, section "Skipping Non-zero

@@ -64,8 +64,10 @@ void prof_end(const Prof& p, int cls, hipStream_t s) {
 // net bound the array last; a net whose binding was taken over refuses to
 // run.
 // (kStaticTables: room for the reference tables of nets that may use the
-// whole limit besides, see st_net::static_extra.)
-constexpr size_t kStaticTables = 256 << 10;
+// whole limit besides, see st_net::static_extra.  They take 112 bytes a layer,
+// of which the limit holds at most one per 2048 bytes: every layer and its
+// tensor have eight buffers of at least 256 bytes.)
+constexpr size_t kStaticTables = ST_STATIC_WORKSPACE_BYTES / 16;
 static __device__ __align__(256) char
     scratch[ST_STATIC_WORKSPACE_BYTES + kStaticTables];
 
@@ -1050,8 +1052,7 @@ extern "C" st_status st_bind_workspace(st_net* net, void* dev_ptr,
 
 extern "C" st_status st_bind_workspace_static(st_net* net, void* stream) {
   if (!net) return fail(nullptr, ST_ERR_INVALID_ARG, "net is NULL");
-  if (net->ws_bytes - net->static_extra > (size_t)ST_STATIC_WORKSPACE_BYTES ||
-      net->static_extra > kStaticTables)
+  if (net->ws_bytes - net->static_extra > (size_t)ST_STATIC_WORKSPACE_BYTES)
     return fail(net, ST_ERR_WORKSPACE,
                 "the net needs " + std::to_string(net->ws_bytes) +
                     " workspace bytes; the static workspace holds " +

@@ -14,7 +14,7 @@ import torch
 from paper_2410_20790_amd import SparseTemNet
 from paper_2410_20790_amd import binding as B
 from parity_util import say, to_dev
-from workloads import toy_net, toy_video
+from workloads import LayerSpec, toy_net, toy_video
 
 pytestmark = pytest.mark.gpu
 
@@ -66,3 +66,24 @@ def test_static_workspace_matches_caller_workspace(thr):
             first.close()
         first = s
     first.close()
+
+
+def test_static_workspace_takes_many_layers():
+    """The reference tables of a residual-carry net (112 bytes a layer) have
+    room beside the static workspace's limit, however many layers it holds."""
+    n = 3000
+    say(f"[gpu] static workspace, {n} layers")
+    rng = np.random.default_rng(17)
+    w = rng.normal(0, 8 ** -0.5, (8, 8, 1, 1)).astype(np.float32)
+    b = np.zeros(8, np.float32)
+    layers = [LayerSpec(src=i - 1, c_in=8, c_out=8, k=(1, 1), s=(1, 1),
+                        p=(0, 0), act=0, weight=w, bias=b) for i in range(n)]
+    x = torch.from_numpy(rng.random((1, 1, 1, 8), np.float32)).cuda()
+    outs = []
+    for static in (True, False):
+        net = SparseTemNet(layers, 1, 1, 1, 8, carry=True,
+                           static_workspace=static)
+        assert net.ws_bytes < B.STATIC_WORKSPACE_BYTES
+        outs.append(net.encode_reference(x).cpu().numpy())
+        net.close()
+    np.testing.assert_array_equal(*outs)
