@@ -2653,13 +2653,15 @@ __global__ __launch_bounds__(256) void k_se_squeeze(SeArgs a) {
     a.part[((int64_t)n * a.nchunk + g) * cp + c] = sm[c];
 }
 
-// Excitation in two launches.  What bounds it is the chain of dependent
-// steps, each a memory round trip or a barrier, on few blocks; one block per
-// image that did it all, a chunk's frames one after another, took 55 us for
-// the seven diff frames of an EfficientNet-B0 layer at 512x512 (now 16) and
-// 11 us for one frame.  Only the channel sums S depend on the frame before, so the means
-// of all frames come first (k_se_means, 64 channels of one image per block),
-// then every frame's and image's gates at once (k_se_gates).
+// Excitation.  What bounds it is the chain of dependent steps, each a memory
+// round trip or a barrier, on few blocks.  Only the channel sums S depend on
+// the frame before, so a chunk takes two launches: the means of all frames
+// (k_se_means, 64 channels of one image per block), then every frame's and
+// image's gates at once (k_se_gates); one block per image that took the frames
+// one after another had 55 us for the seven diff frames of an
+// EfficientNet-B0 layer at 512x512, the two have 16.  A single frame takes one
+// launch (k_se_gates<true>): 8.4 us a layer, where the two have 11.9 and the
+// gap between them (32 images of 256x256: 10.1 and 13.7).
 //
 // Means: a column of 4 channels has `lanes` threads, each summing every
 // lanes-th site chunk's partials of a frame; the lanes' sums are added in lane
@@ -2749,7 +2751,10 @@ __global__ void k_se_means(SeArgs a, int lanes, int cols, int fb) {
 // units (one wave per unit, two units per pass; the first pass's weights are
 // requested before the means), then the gates (each 4-channel output split
 // over Lg thread groups of the hidden units, summed in group order).
+// ONE: a single frame, whose means its block takes itself first (the lanes and
+// sums of k_se_means).
 constexpr int kSeExciteThreads = 1024;
+template <bool ONE>
 __global__ __launch_bounds__(kSeExciteThreads) void k_se_gates(SeArgs a) {
   constexpr int NT = kSeExciteThreads, NW = NT / 64;
   extern __shared__ __align__(16) float sm[];  // [cp] means, [mid], [NT] x4
@@ -2775,8 +2780,32 @@ __global__ __launch_bounds__(kSeExciteThreads) void k_se_gates(SeArgs a) {
     }
   };
   if (wave < a.mid) request(wave);
-  const float* mean = a.part + fr * a.part_stride + (int64_t)n * a.nchunk * cp;
-  for (int c = t; c < cp; c += NT) m[c] = mean[c];
+  const float* part = a.part + fr * a.part_stride + (int64_t)n * a.nchunk * cp;
+  if constexpr (ONE) {
+    const int lanes = NT / V4, v = t % V4, l = t / V4;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (l < lanes) {
+#pragma unroll 4
+      for (int g = l; g < a.nchunk; g += lanes) {
+        const float4 x = ((const float4*)part)[(int64_t)g * V4 + v];
+        acc.x += x.x; acc.y += x.y; acc.z += x.z; acc.w += x.w;
+      }
+    }
+    red[t] = acc;
+    __syncthreads();
+    for (int c = t; c < cp; c += NT) {
+      const float* r = (const float*)red + c;
+      float s = r[0];
+#pragma unroll 16
+      for (int j = 1; j < lanes; ++j) s += r[j * cp];
+      double* S = a.S + (int64_t)n * cp + c;
+      const double sum = (a.ref ? 0.0 : *S) + (double)s;
+      *S = sum;
+      m[c] = (float)(sum / (double)a.hw);
+    }
+  } else {
+    for (int c = t; c < cp; c += NT) m[c] = part[c];
+  }
   __syncthreads();
   // hidden units z = silu(w1 . m + b1)
   const float4* m4 = (const float4*)m;
@@ -2859,20 +2888,24 @@ __global__ __launch_bounds__(kSeExciteThreads) void k_se_gates(SeArgs a) {
 
 static void se_excite(const Prof& pf, hipStream_t s, const SeArgs& a) {
   prof_begin(pf, 20 /*ST_K_SE_EXCITE*/, s);
-  // lanes per column from the channels alone; up to 16 columns a block (64
-  // channels of an image), and as many frames as the block's lane sums allow
-  const int V4 = a.cp / 4, lanes = kSeExciteThreads / V4;
-  const int cols = lanes >= 256 ? 1 : 256 / lanes > 16 ? 16 : 256 / lanes;
-  const int nt = cols * lanes > 256 ? 512 : 256;
-  int fb = kSeMeanVecs / nt;
-  if (fb > kSeMeanTots / (4 * cols)) fb = kSeMeanTots / (4 * cols);
-  if (fb > kSeMeanFrames) fb = kSeMeanFrames;
-  k_se_means<<<dim3((V4 + cols - 1) / cols, a.N), nt, 0, s>>>(
-      a, lanes, cols, fb);
-  k_se_gates<<<dim3(a.N, a.nfr > 1 ? a.nfr : 1), kSeExciteThreads,
-               sizeof(float) * (a.cp + round_up8(a.mid) +
-                                4 * kSeExciteThreads),
-               s>>>(a);
+  const size_t lds = sizeof(float) * (a.cp + round_up8(a.mid) +
+                                      4 * kSeExciteThreads);
+  if (a.nfr > 1) {
+    // lanes per column from the channels alone; up to 16 columns a block (64
+    // channels of an image), and as many frames as the block's lane sums
+    // allow
+    const int V4 = a.cp / 4, lanes = kSeExciteThreads / V4;
+    const int cols = lanes >= 256 ? 1 : 256 / lanes > 16 ? 16 : 256 / lanes;
+    const int nt = cols * lanes > 256 ? 512 : 256;
+    int fb = kSeMeanVecs / nt;
+    if (fb > kSeMeanTots / (4 * cols)) fb = kSeMeanTots / (4 * cols);
+    if (fb > kSeMeanFrames) fb = kSeMeanFrames;
+    k_se_means<<<dim3((V4 + cols - 1) / cols, a.N), nt, 0, s>>>(
+        a, lanes, cols, fb);
+    k_se_gates<false><<<dim3(a.N, a.nfr), kSeExciteThreads, lds, s>>>(a);
+  } else {
+    k_se_gates<true><<<a.N, kSeExciteThreads, lds, s>>>(a);
+  }
   prof_end(pf, 20, s);
 }
 
