@@ -62,3 +62,37 @@ def test_excitation(c, mid, nf, dtype):
         live.close()
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("c,mid", [(24, 3), (264, 17)])
+def test_frozen_gates_of_a_dense_layer(c, mid, dtype):
+    """Frozen gates on a groups=1 layer, frame by frame: every affected row is
+    scaled by its image's gates before and after, from the gate slot of the
+    last reference frame (the second one's is the other slot).  The images and
+    the two references differ in sign, so that the other image's gates or the
+    first reference's are a tenth or more off."""
+    from paper_2410_20790_amd import SparseTemNet
+    net = se_net(c, mid, dtype)
+    net.layers[0].se_w2 *= 4
+    frames = random_sparse_video(5, 6, net.batch, net.H, net.W, 8, 0.4, dtype)
+    for t, f in enumerate(frames):
+        f[t // 3] *= -2
+    o = oracle.OracleNet(net.layers, net.batch, net.H, net.W, 8, dtype,
+                         frozen_se=True)
+    g = SparseTemNet(net.layers, net.batch, net.H, net.W, 8, dtype,
+                     frozen_se=True)
+    thr = [0.0] * 3
+    try:
+        print("frozen gates", c, mid, dtype, flush=True)
+        for t, f in enumerate(frames):
+            x = to_dev(f, dtype)
+            if t % 3 == 0:
+                o.encode_reference(f)
+                out = g.encode_reference(x)
+            else:
+                o.encode_diff(f, thr)
+                out = g.encode_diff(x, thr)
+            assert rel(out.cpu().numpy(), o.last["out"]) <= RTOL[dtype], t
+    finally:
+        g.close()
