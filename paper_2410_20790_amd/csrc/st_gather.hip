@@ -500,10 +500,11 @@ void gather_launch(hipStream_t s, const ConvArgs& a, int step) {
 }
 
 // Stages and blocks per CU (one wave of a block per SIMD): the chunk build
-// keeps 16 state values beside the products and spills at four blocks
-// (ResNet-50 chunk of 9 diff frames: 2.86 ms against 2.65 with three, 2.72
-// with a third stage); the one-frame builds hold four (linear chunk layers
-// 263 us against 302 with three); split reductions are long and take a third
+// keeps 16 state values beside the products and takes three (four, with its
+// spills, 2.86 ms of a ResNet-50 chunk of 9 diff frames against 2.65; three
+// with a third stage 2.72); the one-frame builds take four, although they
+// spill seven to nine registers there, as every mode and activation is in one
+// build (linear chunk layers 263 us against 302 with three); split reductions are long and take a third
 // stage (323 -> 309 us of a frame's).  128x128 tiles (one block per CU) were
 // slower on every layer, and so were the next unit's lists requested ahead.
 template <typename T, bool POINT>

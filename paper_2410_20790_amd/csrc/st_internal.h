@@ -162,7 +162,6 @@ struct st_net {
   int n_counters = 0;
   int n_cleanup = 0, cleanup_blocks = 0;   // table entries, launch blocks
   int n_iota = 0, iota_blocks = 0;
-  int64_t max_grid = 0;
   // runtime
   char* ws = nullptr;
   bool bound = false, have_ref = false;

@@ -208,8 +208,9 @@ struct ConvArgs {
   int64_t gsz;         // floats per slot
   int64_t gate_hw;
   // dense (the reference pass, the REF builds: the state before is zero, the
-  // bias is added): every conv output is a row (row = pixel, nO = capO), every tensor's rows are pixel-ordered, so the neighbours follow
-  // from the geometry g (input row of output o at offset k, or -1 in the
+  // bias is added): every conv output is a row (row = pixel, nO = capO),
+  // every tensor's rows are pixel-ordered, so the neighbours follow from the
+  // geometry g (input row of output o at offset k, or -1 in the
   // padding), the residual row of a pixel is the pixel itself, and no row
   // maximum is kept (rowmax NULL)
   int dense;
@@ -229,7 +230,8 @@ struct ConvArgs {
 // rows of 4 channels).  An f32 net with a bf16 state keeps the gather kernel:
 // the dense convolution adds a stage's f32 columns in another order, and each
 // state that a last-bit difference rounds to the other bf16 neighbour moves
-// by 2^-9 (f16 and bf16 columns are added in the same order by both).
+// by 2^-9 (f16 and bf16 columns are added in the same order and the same
+// parts by both).
 inline bool dense_conv_takes(int dtype, const ConvArgs& a) {
   return dtype == 0 ? a.cin_p % 4 == 0 && !a.p16 : a.cin_p % 8 == 0;
 }

@@ -2591,8 +2591,8 @@ __host__ __device__ __forceinline__ int round_up8(int x) {
 // the affected sites, Mo: site -> dP row).  The pooled mean of f(P) is kept
 // as per-image f64 channel sums S that each frame moves by
 // sum over affected sites of f(P_new) - f(P_old) (in the reference pass,
-// whose states are in P already: by f(P) over every site, from S = 0).  Squeeze: partial sums of that
-// change over fixed site ranges; excite: S, mean and gates per image;
+// whose states are in P already: by f(P) over every site, from S = 0).
+// Squeeze: partial sums of that change over fixed site ranges; excite: S, mean and gates per image;
 // emit: delta = f(P_new) * s_new - f(P_old) * s_old at every site, the state
 // commit, row maxima and the 64-site kept counts.  Every sum runs in a fixed
 // order, so results do not depend on scheduling.
@@ -3485,7 +3485,8 @@ __global__ __launch_bounds__(256) void k_chunk_scan_prep_vec(
 }
 
 // 16-byte vectors of a pixel of C channels if its rows and frames hold whole
-// aligned vectors (1, 2 or 4 of them), else 0.
+// aligned vectors, else 0: 1, 2 or 4 of them, all that a chunk's at most 16
+// channels make (12 f32 channels, three vectors, have padded rows).
 template <typename T>
 static int pixel_vectors(int C, int Cp, const void* x, const void* xhat) {
   const int bytes = C * (int)sizeof(T);

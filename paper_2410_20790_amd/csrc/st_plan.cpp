@@ -227,7 +227,6 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
   // Per-site buffers of the emitted tensors and rulebooks hold F frames
   // (chunk items: frame t's sites follow frame t-1's); the state, X_hat and
   // squeeze-excitation buffers are per physical site.
-  int64_t max_grid = t0.grid * F;
   for (int t = 0; t <= L_n; ++t) {
     TensorPlan& T = net->tensors[t];
     const int64_t items = T.grid * F;
@@ -238,7 +237,6 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
     T.off_act = a.take(sizeof(int32_t) * items);
     T.off_map = a.take(sizeof(int32_t) * items);
     T.off_rowmax = a.take(sizeof(uint32_t) * items);
-    max_grid = std::max(max_grid, items);
   }
   int n_cleanup = L_n + 1;
   size_t part_bytes = 0, chunk_dp_bytes = 0;
@@ -250,7 +248,6 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
     const int64_t citems = L.conv_grid * F;
     L.cnt_pairs = 2 * (L_n + 1) + i;
     L.cnt_sites = 2 * (L_n + 1) + 2 * L_n + kSiteSlots * i;
-    max_grid = std::max(max_grid, citems);
     max_conv_phys = std::max(max_conv_phys, L.conv_grid);
     if (F > 1 && L.stateful)
       chunk_dp_bytes = std::max<size_t>(chunk_dp_bytes,
@@ -319,7 +316,6 @@ static st_status create_impl(const st_layer_desc* layers, int32_t n_layers,
       }
     }
   }
-  net->max_grid = max_grid;
   net->off_flags = a.take(round_up(t0.grid * F, 16));
   if (F > 1) {
     net->off_chunk_dp = a.take(std::max<size_t>(chunk_dp_bytes, 256));
