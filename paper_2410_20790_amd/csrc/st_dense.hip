@@ -549,14 +549,19 @@ void dw_launch(hipStream_t s, const ConvArgs& a, int images) {
       <<<grid, DwTile<T, KS, ST, OCT, TH>::NT, 0, s>>>(a, tiles_x);
 }
 
+// 8 vectors (128 bytes) of a half-precision pixel where that pads the channels
+// by less than half a tile, else 4; f32: 4.
+inline bool dw_wide(int dtype, const ConvArgs& a) {
+  const int rest = a.cout_p / 8 % 8;
+  return dtype != 0 && (rest == 0 || rest > 4);
+}
+
 // Tile height by what the patch leaves of LDS (stride 2: about four input
-// pixels per output); 8 vectors (128 bytes) of a half-precision pixel where
-// that pads the channels by less than half a tile, else 4; f32: 4.
+// pixels per output).
 template <typename T, int KS>
 void dense_dw(hipStream_t s, const ConvArgs& a, int images) {
-  const int rest = a.cout_p / 8 % 8;
   if constexpr (sizeof(T) == 2) {
-    if (rest == 0 || rest > 4) {
+    if (dw_wide(1, a)) {
       if (a.g.sh == 1)
         dw_launch<T, KS, 1, 8, 8>(s, a, images);
       else
@@ -580,6 +585,22 @@ void dense_dw(hipStream_t s, const ConvArgs& a, int images) {
 }
 
 }  // namespace
+
+bool dense_dw_takes(int dtype, const ConvArgs& a, int images) {
+  const Geo& g = a.g;
+  if (images > 65535 || g.kh != g.kw || (g.kh != 3 && g.kh != 5) ||
+      g.sh != g.sw || (g.sh != 1 && g.sh != 2))
+    return false;
+  const bool wide = dw_wide(dtype, a);
+  const int th = (dtype != 0 && !wide ? 16 : 8) / g.sh;
+  const int64_t tiles = (int64_t)((g.Wo + kDwTW - 1) / kDwTW) *
+                        ((g.Ho + th - 1) / th);
+  const int slabs = (a.cout_p / 8 + (wide ? 7 : 3)) / (wide ? 8 : 4);
+  // sixteenths of the tiles' pixels that are outputs
+  const int64_t full = 16 * (int64_t)g.Ho * g.Wo / (tiles * th * kDwTW);
+  if (g.sh == 1) return images * tiles * slabs <= 1024 || full >= 3;
+  return images * tiles * slabs <= 512 || full >= (dtype == 0 ? 10 : 6);
+}
 
 void launch_dense_dw(const Prof& pf, hipStream_t s, int dtype,
                      const ConvArgs& a, int images) {

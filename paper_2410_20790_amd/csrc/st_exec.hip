@@ -475,7 +475,7 @@ static st_status encode_reference(st_net* net, const void* frame, float* out,
     a.dense = 1;
     a.offset_order = net->carry || net->has_se;
     a.g = conv_geo(L);
-    if (L.dw && net->N <= 65535 && dense_dw_takes(a))  // (an image per grid row)
+    if (L.dw && dense_dw_takes(net->dtype, a, net->N))
       launch_dense_dw(pfl, s, net->dtype, a, net->N);
     else if (L.dw)
       launch_conv_dw(pfl, s, net->dtype, a);

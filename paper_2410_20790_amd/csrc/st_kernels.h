@@ -237,11 +237,14 @@ inline bool dense_conv_takes(int dtype, const ConvArgs& a) {
 }
 int launch_dense_conv(hipStream_t s, int dtype, const ConvArgs& a);
 // Dense pass: a depthwise convolution with a 3x3 or 5x5 window of stride 1 or
-// 2 (dense_dw_takes).
-inline bool dense_dw_takes(const ConvArgs& a) {
-  return a.g.kh == a.g.kw && (a.g.kh == 3 || a.g.kh == 5) &&
-         a.g.sh == a.g.sw && (a.g.sh == 1 || a.g.sh == 2);
-}
+// 2.  Its block costs the same however few of its tile's pixels are outputs:
+// on small maps it pays while the launch's blocks are few (its chain of steps
+// is the shorter one), or from the share of outputs on at which a block beats
+// the row kernel (k_conv_dw).  5x5 over 1152 channels, f16, us there and here:
+// 1 image of 4x4 14.2 and 7.1; 300 images stride 1, 3x3 31 and 48, 5x5 70 and
+// 52, 8x8 162 and 55; stride 2, 4x4 52 and 82, 8x8 194 and 168; f32 stride 2,
+// 8x8 274 and 333.  An image is a grid row: at most 65,535.
+bool dense_dw_takes(int dtype, const ConvArgs& a, int images);
 void launch_dense_dw(const Prof& pf, hipStream_t s, int dtype,
                      const ConvArgs& a, int images);
 // The gathered convolutions of a diff frame or a chunk that st_gather.hip

@@ -216,6 +216,11 @@ DW_CASES = [
     ("bf16", 1, 70, 131, 32, 3, 1, 8),
     ("f32", 1, 11, 12, 16, 5, 2, 0),
     ("bf16", 65536, 1, 2, 8, 3, 1, 0),
+    # many small maps: by rows, or from a share of a tile on by patches
+    ("f16", 120, 3, 4, 136, 3, 1, 0),
+    ("f32", 60, 6, 5, 152, 5, 1, 4),
+    ("bf16", 90, 9, 8, 64, 5, 2, 0),
+    ("f32", 70, 16, 15, 72, 3, 2, 0),
 ]
 
 
