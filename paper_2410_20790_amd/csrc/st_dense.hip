@@ -356,7 +356,10 @@ void dense_launch(hipStream_t s, const ConvArgs& a, int parts) {
 // the layers of a ResNet-50 at 1024x2048, bf16, us):
 //  - 128x128, 3 stages, where that still makes 224 tiles: half the operand
 //    traffic of 64x64 (512->256 on 32768 pixels: 27 against 32; 1024->512 on
-//    8192: 18 against 24), one block of eight waves per CU;
+//    8192: 18 against 24), one block of eight waves per CU (f32, which the
+//    products bound: where the CU with the most tiles then has at most 15%
+//    more products to do than with 128x64 tiles; 3x3 256 on 19200 pixels
+//    309 against 244, 1152->192 on 50176 307 against 207);
 //  - 128x64 where that makes 224 tiles: two blocks per CU with 3 stages (3x3
 //    256 on 8192 pixels: 21 against 28 for 128x128), three with 2 stages when
 //    the tiles go round the chip several times (3x3 64 on 131072: 27 against
@@ -370,7 +373,9 @@ void dense_tiles(hipStream_t s, const ConvArgs& a, int parts) {
   const int64_t n64 = (a.cout_p + 63) / 64, n128 = (a.cout_p + 127) / 128;
   if (a.cout_p <= 32 && m128 >= 224)
     dense_launch<T, 128, 32, 32, 32, 3, SUM>(s, a, parts);
-  else if (a.cout_p > 64 && m128 * n128 >= 224)
+  else if (a.cout_p > 64 && m128 * n128 >= 224 &&
+           (sizeof(T) == 2 ||
+            40 * ((m128 * n128 + 255) / 256) <= 23 * ((m128 * n64 + 255) / 256)))
     dense_launch<T, 128, 128, 64, 32, 3, SUM>(s, a, parts);
   else if (SUM == kSumChain && m128 * n64 >= 1024)  // (parts: 1023 of 64x64)
     dense_launch<T, 128, 64, 32, 32, 2, kSumChain>(s, a, 1);

@@ -40,6 +40,8 @@ CASES = [
     ("bf16", 1, 171, 169, 128, 120, 1, 1, 0),
     ("f16", 1, 120, 121, 64, 200, 3, 1, 1),
     ("f32", 1, 121, 120, 24, 136, 1, 1, 0),
+    # f32 of a little more than two tiles of 128x128 per CU: 128x64
+    ("f32", 1, 170, 170, 16, 136, 1, 1, 0),
 ]
 
 
