@@ -4164,8 +4164,12 @@ __global__ __launch_bounds__(256) void k_dense_input(const T* x, T* xhat,
 void launch_dense_input(const Prof& pf, hipStream_t s, int dtype,
                         const void* x, void* xhat, void* rows, int C, int Cp,
                         int64_t npix) {
-  const int nv = dtype == 0 ? pixel_vectors<float>(C, Cp, x, xhat)
-                            : pixel_vectors<_Float16>(C, Cp, x, xhat);
+  // (as pixel_vectors, for any number of vectors)
+  const int bytes = C * (dtype == 0 ? 4 : 2);
+  const int nv = C == Cp && bytes % 16 == 0 &&
+                         (((uintptr_t)x | (uintptr_t)xhat) & 15) == 0
+                     ? bytes / 16
+                     : 0;
   const int grid = grid_for(npix * (nv ? nv : 1), 8192);
   prof_begin(pf, 1 /*ST_K_SCAN_COMPACT*/, s);
   if (dtype == 0)
