@@ -316,10 +316,14 @@ def measured_peaks():
 
 
 def kernel_source_hash():
+    """One hash over every file the kernels are compiled from."""
     import hashlib
-    src = os.path.join(ROOT, "paper_2410_20790_amd", "csrc",
-                       "st_kernels.hip")
-    return hashlib.sha256(open(src, "rb").read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for f in ("st_kernels.hip", "st_dense.hip", "st_gather.hip",
+              "st_stage.h", "st_device.h", "st_kernels.h", "st_modes.h"):
+        h.update(open(os.path.join(ROOT, "paper_2410_20790_amd", "csrc", f),
+                      "rb").read())
+    return h.hexdigest()[:16]
 
 
 def measured_traffic(workload_desc, kernel):
@@ -338,6 +342,7 @@ def measured_traffic(workload_desc, kernel):
 
 
 KCLASS = {"k_conv_gemm": "conv_gemm", "k_conv_gemm_big": "conv_gemm",
+          "k_gather_conv": "conv_gemm",
           "k_conv_dw": "conv_dw",
           "k_split_epi": "conv_split_epi", "k_pool_emit": "pool_emit",
           "k_commit": "commit", "k_output": "output",
@@ -374,7 +379,7 @@ def demangle_st(name):
     (c++filt does not know _Float16's DF16_): st::<name><args>, the
     arguments being the storage types, predicate structs and bools/ints."""
     import re
-    m = re.match(r"_ZN2st(\d+)", name)
+    m = re.match(r"_ZN2st(?:12_GLOBAL__N_1)?(\d+)", name)
     if not m:
         return name
     n = int(m.group(1))
@@ -422,18 +427,24 @@ def demangle_st(name):
     return f"st::{fn}<{', '.join(args)}>"
 
 
+def kernel_head(kernel_name):
+    """The kernel's readable name with its template arguments, without its
+    return type, parameters and unnamed namespace."""
+    name = demangle(kernel_name).replace("(anonymous namespace)::", "")
+    return name.split("(")[0].replace("void ", "", 1)
+
+
 def kernel_class(kernel_name):
     """Kernel class of a traced kernel name, None for kernels outside the
     diff pass (reference-pass instantiations, library kernels)."""
-    head = demangle(kernel_name).split("(")[0]
-    if head.startswith("void "):
-        head = head[5:]
+    head = kernel_head(kernel_name)
     fn = head.split("<")[0].split("::")[-1]
     targs = (head.split("<", 1)[1].rstrip(">").split(", ")
              if "<" in head else [])
     if fn == "k_compact":
         return PCLASS.get(targs[0].split("<")[0].split("::")[-1])
-    if fn == "k_chunk_scan_prep":
+    if fn in ("k_chunk_scan_prep", "k_chunk_scan_prep_rgb8",
+              "k_chunk_scan_prep_vec"):
         return "chunk_scan_mask"
     if fn == "k_chunk_xhat_commit":
         return "chunk_xhat_commit"
@@ -446,7 +457,7 @@ def kernel_class(kernel_name):
 
 
 def ingest_mfma(base, workload_name, density, schedule=None):
-    """MFMA utilisation of the diff-pass gather-GEMM from one rocprofv3
+    """MFMA utilisation of the convolution kernels from one rocprofv3
     --pmc run (DIR/pmc_mfma): per dispatch, the cycles the MFMA units were
     busy summed over every SIMD over (GPU-active cycles x 1024 SIMDs), the
     MFMA work issued (MOPS x 512 FLOP) and its rate over the dispatch's
@@ -460,9 +471,10 @@ def ingest_mfma(base, workload_name, density, schedule=None):
     for r in csv.DictReader(open(path)):
         raw = r["Kernel_Name"]
         if raw not in names:
-            names[raw] = demangle(raw).split("(")[0].replace("void ", "")
+            names[raw] = kernel_head(raw)
         name = names[raw]
-        if not name.startswith("st::k_conv_gemm"):
+        if not name.startswith(("st::k_conv_gemm", "st::k_gather_conv",
+                                "st::k_dense_conv")):
             continue
         d = disp[r["Dispatch_Id"]]
         d["name"] = name
