@@ -17,8 +17,9 @@
 // another, go through LDS.
 //
 // Measured (us of kernel time, before -> after): two live ResNet-50 frames at
-// 1024x2048 2000 -> 1580; the linear and small chunk layers of its chunk of 9
-// 3020 -> 2910; EfficientNet-B0's 1x1 layers, whose channels fill no stage
+// 1024x2048 2000 -> 1580; in its chunk of 9 the seven 3x3 layers here 405 ->
+// 367 and the fourteen 1x1 layers without a residual row 767 -> 750;
+// EfficientNet-B0's 1x1 layers, whose channels fill no stage
 // (and paid a division per vector), of 32 cameras 650 -> 420.
 #include <hip/hip_runtime.h>
 
@@ -504,9 +505,14 @@ void gather_launch(hipStream_t s, const ConvArgs& a, int step) {
 // spills, 2.86 ms of a ResNet-50 chunk of 9 diff frames against 2.65; three
 // with a third stage 2.72); the one-frame builds take four, although they
 // spill seven to nine registers there, as every mode and activation is in one
-// build (linear chunk layers 263 us against 302 with three); split reductions are long and take a third
-// stage (323 -> 309 us of a frame's).  128x128 tiles (one block per CU) were
-// slower on every layer, and so were the next unit's lists requested ahead.
+// build (linear chunk layers 263 us against 302 with three).  Split
+// reductions are long and take a third stage (323 -> 309 us of a frame's),
+// and so do, in chunks of long runs, half-precision 1x1 layers of four stages
+// or more (the fourteen without a residual row of a ResNet-50 chunk of 9:
+// 793 -> 750 us with 10% of the sites changed, 2050 -> 1946 with 40%; the 3x3
+// layers 367 -> 381, f32 chunks 4.75 -> 4.80 ms).  128x128 tiles (one block
+// per CU) were slower on every layer, and so were the next unit's lists
+// requested ahead.
 template <typename T, bool POINT>
 void gather_conv(hipStream_t s, const ConvArgs& a) {
   if (a.mode == kModeChunkState && a.nf <= kGatherShortRuns)

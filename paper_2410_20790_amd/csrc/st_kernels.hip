@@ -2592,10 +2592,10 @@ __host__ __device__ __forceinline__ int round_up8(int x) {
 // as per-image f64 channel sums S that each frame moves by
 // sum over affected sites of f(P_new) - f(P_old) (in the reference pass,
 // whose states are in P already: by f(P) over every site, from S = 0).
-// Squeeze: partial sums of that change over fixed site ranges; excite: S, mean and gates per image;
-// emit: delta = f(P_new) * s_new - f(P_old) * s_old at every site, the state
-// commit, row maxima and the 64-site kept counts.  Every sum runs in a fixed
-// order, so results do not depend on scheduling.
+// Squeeze: partial sums of that change over fixed site ranges; excite: S, mean
+// and gates per image; emit: delta = f(P_new) * s_new - f(P_old) * s_old at
+// every site, the state commit, row maxima and the 64-site kept counts.  Every
+// sum runs in a fixed order, so results do not depend on scheduling.
 //
 // Row mapping: TPS threads per site (a power of two up to one wave), each
 // owning the 8-channel vectors lane, lane + TPS, ... (at most 4 of them for
