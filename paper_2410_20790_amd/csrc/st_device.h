@@ -110,6 +110,36 @@ template <typename T> struct Vec8Half {
 template <> struct Vec8<_Float16> : Vec8Half<_Float16> {};
 template <> struct Vec8<bf16_t> : Vec8Half<bf16_t> {};
 
+// Stores a[e] * b[e] - c[e], f16 rounded once from the exact product and
+// difference (the mixed-precision multiply-add; left to the compiler it is
+// that or an f32 result rounded again, by how it vectorised the code around);
+// returns what Vec8::store of the f32 results would.
+template <typename T>
+__device__ __forceinline__ float store8_fma(T* p, const float* a,
+                                            const float* b, const float* c) {
+  float f[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) f[e] = __builtin_fmaf(a[e], b[e], -c[e]);
+  if constexpr (__is_same(T, _Float16)) {
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t* h = (uint32_t*)&v;
+    float m = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+      asm("v_fma_mixlo_f16 %0, %1, %2, -%3"
+          : "+v"(h[e / 2])
+          : "v"(a[e]), "v"(b[e]), "v"(c[e]));
+      asm("v_fma_mixhi_f16 %0, %1, %2, -%3"
+          : "+v"(h[e / 2])
+          : "v"(a[e + 1]), "v"(b[e + 1]), "v"(c[e + 1]));
+      m = fmaxf(m, fmaxf(fabsf(f[e]), fabsf(f[e + 1])));
+    }
+    *(uint4*)p = v;
+    return to_f(from_f<_Float16>(m));
+  } else {
+    return Vec8<T>::store(p, f);
+  }
+}
 
 __device__ __forceinline__ void load8f(const float* p, float* f) {
   Vec8<float>::load(p, f);

@@ -3217,7 +3217,7 @@ __device__ __forceinline__ void chunk_se_emit_site(const ChunkSeArgs& a,
     for (int k = 0; k < IT; ++k) {
       const int v = lane + k * TPS;
       if (v >= V) break;
-      float fn[8], g1[8], d[8];
+      float fn[8], g1[8], old[8];
       load8f(gn + v * 8, g1);
       if (r >= 0) {
         load8f(a.Pt + (int64_t)r * cp + v * 8, fn);
@@ -3229,11 +3229,11 @@ __device__ __forceinline__ void chunk_se_emit_site(const ChunkSeArgs& a,
       }
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        d[e] = fn[e] * g1[e] - fo[k][e] * go[k][e];
+        old[e] = fo[k][e] * go[k][e];
         fo[k][e] = fn[e];
         go[k][e] = g1[e];
       }
-      rm = fmaxf(rm, Vec8<T>::store(dout + j * cp + v * 8, d));
+      rm = fmaxf(rm, store8_fma<T>(dout + j * cp + v * 8, fn, g1, old));
     }
 #pragma unroll
     for (int o = 1; o < TPS; o <<= 1) rm = fmaxf(rm, __shfl_xor(rm, o, 64));

@@ -96,3 +96,35 @@ def test_frozen_gates_of_a_dense_layer(c, mid, dtype):
             assert rel(out.cpu().numpy(), o.last["out"]) <= RTOL[dtype], t
     finally:
         g.close()
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("c", [32, 264])
+def test_chunk_rows_round_as_live_rows(c, dtype):
+    """The emitted rows of a squeeze-excitation layer in a chunk are bit for
+    bit those of its frames encoded one by one: f(P) s - f(P') s' is rounded
+    to the storage type once, without an f32 rounding before."""
+    from paper_2410_20790_amd import SparseTemNet
+    from paper_2410_20790_amd import binding as B
+    nf, sites = 6, 2 * 40 * 37
+    net = se_net(c, 9, dtype, H=40, W=37)
+    frames = random_sparse_video(7, nf + 1, 2, 40, 37, 8, 0.3, dtype)
+    frames = [to_dev(f, dtype) for f in frames]
+    thr = [0.0] * 3
+    print("chunk rows", c, dtype, flush=True)
+    nets = [SparseTemNet(net.layers, 2, 40, 37, 8, dtype, max_frames=n)
+            for n in (nf, 1)]
+    try:
+        for g in nets:
+            g.encode_reference(frames[0])
+        nets[0].encode_chunk(torch.stack(frames[1:]), thr)
+        pix, rows = B.st_debug_candidates(nets[0].handle, 0, c)
+        chunk = np.empty((nf * sites, c), np.float32)
+        chunk[pix] = rows
+        for t in range(nf):
+            nets[1].encode_diff(frames[t + 1], thr)
+            pix, rows = B.st_debug_candidates(nets[1].handle, 0, c)
+            assert np.array_equal(chunk[t * sites + pix], rows), t
+    finally:
+        for g in nets:
+            g.close()
