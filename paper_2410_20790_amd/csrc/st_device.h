@@ -149,13 +149,14 @@ __device__ __forceinline__ void store8f(float* p, const float* f) {
   *(float4*)(p + 4) = make_float4(f[4], f[5], f[6], f[7]);
 }
 
-// The values a row of type T holds after rounding, as f32 (the view that a
-// residual-carry reference frame starts from its emitted rows).
+// The values a row of type T holds after rounding, as f32, added to zero (the
+// view that a residual-carry reference frame starts from its emitted rows: no
+// -0, as in a view that rows were added to).
 template <typename T>
 __device__ __forceinline__ void store8f_rounded(float* p, const float* f) {
   float r[8];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = to_f(from_f<T>(f[e]));
+  for (int e = 0; e < 8; ++e) r[e] = to_f(from_f<T>(f[e])) + 0.f;
   store8f(p, r);
 }
 

@@ -134,3 +134,21 @@ def test_residual_carry_in_chunks(name, net, frames, thr, F):
     finally:
         c.close()
         f.close()
+
+
+def test_view_of_the_reference_has_no_negative_zero():
+    """The view starts from zero and the reference frame's rows are added to
+    it: a row value that rounds to -0 leaves 0."""
+    from paper_2410_20790_amd import SparseTemNet
+    from workloads import LayerSpec
+    L = LayerSpec(src=-1, c_in=8, c_out=8, k=(1, 1), s=(1, 1), p=(0, 0),
+                  act=2, weight=np.zeros((8, 8, 1, 1), np.float32),
+                  bias=np.full((8,), -30, np.float32))
+    net = SparseTemNet([L], 1, 5, 7, 8, "f16", carry=True)
+    try:
+        net.encode_reference(torch.ones((1, 5, 7, 8), dtype=torch.float16,
+                                        device="cuda"))
+        view = B.st_debug_carry(net.handle, 0, (1, 5, 7, 8))
+    finally:
+        net.close()
+    assert not view.any() and not np.signbit(view).any()
